@@ -342,7 +342,7 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
     return launch_2d<Pop, S, R>(c->p.nphase, mode, c->kd, k, b, c->tile_y,
                                 c->stream);
   return launch_3d<Pop, S, R>(c->p.nphase, c->p.lattice_f, mode, c->kd, k, b,
-                              c->tile_x, c->tile_y, c->stream);
+                              c->tile_x, c->tile_y, c->cus, c->stream);
 }
 
 hipError_t launch(ddcc_ctx* c, int mode, const double* inC, const double* inU,
@@ -507,7 +507,9 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   // from 4096^2 down to 128^2), 64 x 8 for float; 3D: 64 x 4 columns.
   c->tile_y = d == 2 ? (p->precision == DDCC_FP64 ? 4 : 8) : 4;
   c->tile_x = 64;
-  if (hipGetDevice(&c->device) != hipSuccess) {
+  if (hipGetDevice(&c->device) != hipSuccess ||
+      hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount,
+                            c->device) != hipSuccess) {
     delete c;
     return DDCC_E_HIP;
   }

@@ -17,6 +17,7 @@ struct ddcc_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   int device = 0;
+  int cus = 0;  // compute units of the device
   long long n = 0;
   int Qf = 0, Qg = 0, nhist = 0, nT = 0;
   size_t esz = 8;   // history, T and geometry fields

@@ -66,11 +66,13 @@ hipError_t launch_2d(int nphase, int mode, const Coef<double>& kd,
                      const Coef<R>& k, const Bufs<Pop, S>& b, int ty,
                      hipStream_t st);
 
-// lattice_f: the phase-set lattice id (D3Q15 or D3Q7 of lattice.hpp).
+// lattice_f: the phase-set lattice id (D3Q15 or D3Q7 of lattice.hpp); cus:
+// compute units of the device.
 template <class Pop, class S, class R>
 hipError_t launch_3d(int nphase, int lattice_f, int mode,
                      const Coef<double>& kd, const Coef<R>& k,
-                     const Bufs<Pop, S>& b, int tx, int ty, hipStream_t st);
+                     const Bufs<Pop, S>& b, int tx, int ty, int cus,
+                     hipStream_t st);
 
 // Batches of independent 2D boxes: one work-queue entry per tile, and the
 // size and node offset of every instance. Each plane of each buffer holds

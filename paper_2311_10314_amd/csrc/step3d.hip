@@ -16,7 +16,7 @@
 //             post-collision populations written at the node (pull
 //             streaming).
 // k_frac3d runs one node per thread. k_mu3d and k_step3d give each
-// workgroup a 64 x TY column of nodes over ZB planes and march it in z with
+// workgroup a 64 x TY column of nodes over zb planes and march it in z with
 // three planes of their stencil fields (C_j, psi; and mu_i for the step) in
 // an LDS ring, so each value is fetched once per tile instead of once per
 // neighbour. The C and mu fields (in the field type: float64 for FP64
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(TX* TY) void k_frac3d(Coef<double> k,
 }
 
 // ---- k_mu3d ---------------------------------------------------------------
-// z-marching: a workgroup owns a TX x TY column of nodes over ZB planes and
+// z-marching: a workgroup owns a TX x TY column of nodes over zb planes and
 // keeps three planes of C_j and psi (tile plus a one-node halo) in an LDS
 // ring, so each value is fetched once per tile instead of once per
 // neighbour (the 19-point stencil otherwise issues 19 loads per node and
@@ -248,14 +248,16 @@ __global__ __launch_bounds__(TX* TY) void k_frac3d(Coef<double> k,
 // same GPU). The step kernel's ring stays float64: typed as the fields it
 // took more registers and was slower (FP32 2.69 -> 2.73 ms, FP16 1.89 ->
 // 2.81 ms per step).
-// Planes per workgroup: each column reloads two halo planes, but more
-// columns run at once (same GPU, 256^3 per step, 16 -> 8 planes: FP32 2.86 ->
-// 2.80 ms, FP16 and BF16 0.5 % faster, FP64 unchanged; 4 planes: FP32 2.78
-// ms, the others 1 % slower than at 16; 32 planes slower for all).
+// Planes per workgroup: at most ZB. Each column reloads two halo planes, but
+// more columns run at once (same GPU, 256^3 per step, 16 -> 8 planes: FP32
+// 2.86 -> 2.80 ms, FP16 and BF16 0.5 % faster, FP64 unchanged; 4 planes: FP32
+// 2.78 ms, the others 1 % slower than at 16; 32 planes slower for all).
+// Boxes whose columns of ZB planes leave the chip partly idle take shorter
+// ones (planes_per_group).
 constexpr int ZB = 8;
 
 template <int N, class Pop, class S, int TY, bool NT>
-__global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b) {
+__global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b, int zb) {
   // arithmetic in the field type: float64 in FP64 contexts, float32 otherwise
   using D = std::conditional_t<std::is_same_v<S, double>, double, float>;
   constexpr int HX = TX + 2, HY = TY + 2, HN = HX * HY;
@@ -275,8 +277,8 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b)
     by = t / gx;
   }
   const int x0 = int(bx) * TX, y0 = int(by) * TY;
-  const int z0 = int(blockIdx.z) * ZB;
-  const int z1 = z0 + ZB < nz ? z0 + ZB : nz;
+  const int z0 = int(blockIdx.z) * zb;
+  const int z1 = z0 + zb < nz ? z0 + zb : nz;
   const int tx = int(threadIdx.x) % TX, ty = int(threadIdx.x) / TX;
   const int x = x0 + tx, y = y0 + ty;
   const bool own = x < nx && y < ny;
@@ -817,7 +819,7 @@ __global__ __launch_bounds__(TX* TY)
 __attribute__((amdgpu_waves_per_eu(step3d_waves<N, TY>())))
 void k_step3d(Coef<double> kda, Coef<R> ka,
               const Coef<double>* __restrict__ kdp,
-              const Coef<R>* __restrict__ kp, Bufs<Pop, S> b) {
+              const Coef<R>* __restrict__ kp, Bufs<Pop, S> b, int zb) {
   // Coefficients as kernel arguments overflow the scalar registers and spill
   // into VGPR lanes; read from a device table they cost no spills but scalar
   // loads inside the z loop. Which is faster depends on the storage type
@@ -842,8 +844,8 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
     by = t / gx;
   }
   const int x0 = int(bx) * TX, y0 = int(by) * TY;
-  const int z0 = int(blockIdx.z) * ZB;
-  const int z1 = z0 + ZB < nz ? z0 + ZB : nz;
+  const int z0 = int(blockIdx.z) * zb;
+  const int z1 = z0 + zb < nz ? z0 + zb : nz;
   const int tx = int(threadIdx.x) % TX, ty = int(threadIdx.x) / TX;
   const int x = x0 + tx, y = y0 + ty;
   const bool own = x < nx && y < ny;
@@ -964,50 +966,100 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
   }
 }
 
+// Planes per workgroup (8, 4, 2 or 1, at least `least`) for `tiles` columns
+// over nz planes on a chip that holds `slots` workgroups at once. Columns run
+// in ceil(workgroups / slots) rounds, and a round lasts as long as its planes
+// plus the start of a column, `start` planes' worth: shorter columns fill an
+// idle chip or an emptier last round, longer ones start less often. Columns
+// of ZB, 4, 2 and 1 planes in k_step3d, us per step (same GPU): 64^3 FP64 141
+// / 92 / 83 / 85, FP32 77 / 54 / 45 / 51; 40^3 FP16 79 / 45 / 31 / 26; 130 x 75
+// x 101 N = 3 D3Q7 FP32 272 / 247 / 242 / 259; 110 x 100 x 90 N = 3 D3Q15 FP32
+// 373 / 325 / 306 / 310; 128^3 FP32 312 / 310 / 318 / 334 (there and above
+// every round is full and ZB stays).
+inline int planes_per_group(int nz, int tiles, int slots, double start,
+                            int least) {
+  int best = ZB;
+  double cost = 0;
+  for (int zb = ZB; zb >= least; zb /= 2) {
+    const long long wgs = (long long)tiles * ((nz + zb - 1) / zb);
+    const double c = double((wgs + slots - 1) / slots) * (zb + start);
+    if (zb == ZB || c < cost) {
+      cost = c;
+      best = zb;
+    }
+  }
+  return best;
+}
+
+// Workgroups of `kernel` that one compute unit holds.
+template <class K>
+int groups_per_cu(K* kernel, int threads) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &per_cu, reinterpret_cast<const void*>(kernel), threads, 0) !=
+      hipSuccess)
+    return 2;
+  return per_cu < 1 ? 1 : per_cu;
+}
+
 template <int N, class LF, class Pop, class S, class R, int MODE, int TY>
 hipError_t launch_3(const Coef<double>& kd, const Coef<R>& k,
-                    const Bufs<Pop, S>& b, hipStream_t st) {
+                    const Bufs<Pop, S>& b, int cus, hipStream_t st) {
+  if (!b.coef_d || !b.coef_r) return hipErrorInvalidValue;
   const dim3 g((k.nx + TX - 1) / TX, (k.ny + TY - 1) / TY, k.nz);
   const dim3 blk(TX * TY);
-  hipLaunchKernelGGL((k_frac3d<N, LF, Pop, S, R, MODE, TY>), g, blk, 0, st, kd, b);
+  constexpr auto* frac = &k_frac3d<N, LF, Pop, S, R, MODE, TY>;
+  constexpr auto* mu = &k_mu3d<N, Pop, S, TY, MODE == MODE_STREAM>;
+  constexpr auto* step = &k_step3d<N, LF, D3Q19, Pop, S, R, MODE, TY>;
+  // constants of the code object, looked up once
+  static const int mu_per_cu = groups_per_cu(mu, TX * TY);
+  static const int step_per_cu = groups_per_cu(step, TX * TY);
+  const int tiles = int(g.x * g.y);
+  hipLaunchKernelGGL(frac, g, blk, 0, st, kd, b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 gm(g.x, g.y, (k.nz + ZB - 1) / ZB);
-  hipLaunchKernelGGL((k_mu3d<N, Pop, S, TY, MODE == MODE_STREAM>), gm, blk, 0,
-                     st, kd, b);
+  const int zm = planes_per_group(k.nz, tiles, cus * mu_per_cu, 2.0, 2);
+  const dim3 gm(g.x, g.y, (k.nz + zm - 1) / zm);
+  hipLaunchKernelGGL(mu, gm, blk, 0, st, kd, b, zm);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (!b.coef_d || !b.coef_r) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_step3d<N, LF, D3Q19, Pop, S, R, MODE, TY>), gm, blk, 0,
-                     st, kd, k, static_cast<const Coef<double>*>(b.coef_d),
-                     static_cast<const Coef<R>*>(b.coef_r), b);
+  const int zs = planes_per_group(k.nz, tiles, cus * step_per_cu, 0.5, 1);
+  const dim3 gs(g.x, g.y, (k.nz + zs - 1) / zs);
+  hipLaunchKernelGGL(step, gs, blk, 0, st, kd, k,
+                     static_cast<const Coef<double>*>(b.coef_d),
+                     static_cast<const Coef<R>*>(b.coef_r), b, zs);
   return hipGetLastError();
 }
 
 template <int N, class Pop, class S, class R, int MODE>
 hipError_t launch_ty3(int lattice_f, const Coef<double>& kd, const Coef<R>& k,
-                      const Bufs<Pop, S>& b, int ty, hipStream_t st) {
+                      const Bufs<Pop, S>& b, int ty, int cus,
+                      hipStream_t st) {
   if (lattice_f == D3Q7::ID) {
-    if (ty == 2) return launch_3<N, D3Q7, Pop, S, R, MODE, 2>(kd, k, b, st);
-    return launch_3<N, D3Q7, Pop, S, R, MODE, 4>(kd, k, b, st);
+    if (ty == 2) return launch_3<N, D3Q7, Pop, S, R, MODE, 2>(kd, k, b, cus, st);
+    return launch_3<N, D3Q7, Pop, S, R, MODE, 4>(kd, k, b, cus, st);
   }
-  if (ty == 2) return launch_3<N, D3Q15, Pop, S, R, MODE, 2>(kd, k, b, st);
-  return launch_3<N, D3Q15, Pop, S, R, MODE, 4>(kd, k, b, st);
+  if (ty == 2) return launch_3<N, D3Q15, Pop, S, R, MODE, 2>(kd, k, b, cus, st);
+  return launch_3<N, D3Q15, Pop, S, R, MODE, 4>(kd, k, b, cus, st);
 }
 
 template <int N, class Pop, class S, class R>
 hipError_t launch_mode3(int mode, int lattice_f, const Coef<double>& kd,
                         const Coef<R>& k, const Bufs<Pop, S>& b, int ty,
-                        hipStream_t st) {
+                        int cus, hipStream_t st) {
   switch (mode) {
     case MODE_STEP:
-      return launch_ty3<N, Pop, S, R, MODE_STEP>(lattice_f, kd, k, b, ty, st);
+      return launch_ty3<N, Pop, S, R, MODE_STEP>(lattice_f, kd, k, b, ty, cus,
+                                                   st);
     case MODE_STREAM:
-      return launch_ty3<N, Pop, S, R, MODE_STREAM>(lattice_f, kd, k, b, ty, st);
+      return launch_ty3<N, Pop, S, R, MODE_STREAM>(lattice_f, kd, k, b, ty, cus,
+                                                   st);
     case MODE_INIT:
-      return launch_ty3<N, Pop, S, R, MODE_INIT>(lattice_f, kd, k, b, ty, st);
+      return launch_ty3<N, Pop, S, R, MODE_INIT>(lattice_f, kd, k, b, ty, cus,
+                                                   st);
     default:
-      return launch_ty3<N, Pop, S, R, MODE_MOMENTS>(lattice_f, kd, k, b, ty, st);
+      return launch_ty3<N, Pop, S, R, MODE_MOMENTS>(lattice_f, kd, k, b, ty, cus,
+                                                   st);
   }
 }
 
@@ -1016,14 +1068,16 @@ hipError_t launch_mode3(int mode, int lattice_f, const Coef<double>& kd,
 template <class Pop, class S, class R>
 hipError_t launch_3d(int nphase, int lattice_f, int mode,
                      const Coef<double>& kd, const Coef<R>& k,
-                     const Bufs<Pop, S>& b, int tx, int ty, hipStream_t st) {
+                     const Bufs<Pop, S>& b, int tx, int ty, int cus,
+                     hipStream_t st) {
   (void)tx;
+  if (cus < 1) return hipErrorInvalidValue;
   if (!b.fC || !b.fmu) return hipErrorInvalidValue;
   switch (nphase) {
     case 2:
-      return launch_mode3<2, Pop, S, R>(mode, lattice_f, kd, k, b, ty, st);
+      return launch_mode3<2, Pop, S, R>(mode, lattice_f, kd, k, b, ty, cus, st);
     case 3:
-      return launch_mode3<3, Pop, S, R>(mode, lattice_f, kd, k, b, ty, st);
+      return launch_mode3<3, Pop, S, R>(mode, lattice_f, kd, k, b, ty, cus, st);
     default:
       return hipErrorInvalidValue;
   }
@@ -1031,15 +1085,15 @@ hipError_t launch_3d(int nphase, int lattice_f, int mode,
 
 template hipError_t launch_3d<double, double, double>(
     int, int, int, const Coef<double>&, const Coef<double>&,
-    const Bufs<double, double>&, int, int, hipStream_t);
+    const Bufs<double, double>&, int, int, int, hipStream_t);
 template hipError_t launch_3d<float, float, float>(
     int, int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<float, float>&, int, int, hipStream_t);
+    const Bufs<float, float>&, int, int, int, hipStream_t);
 template hipError_t launch_3d<_Float16, float, float>(
     int, int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<_Float16, float>&, int, int, hipStream_t);
+    const Bufs<_Float16, float>&, int, int, int, hipStream_t);
 template hipError_t launch_3d<__bf16, float, float>(
     int, int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<__bf16, float>&, int, int, hipStream_t);
+    const Bufs<__bf16, float>&, int, int, int, hipStream_t);
 
 }  // namespace ddcc
