@@ -269,8 +269,8 @@ int ddcc_objective(ddcc_ctx* ctx, int phase, const double* weight, double* J);
 
 /* Kernel launch shape of the step kernel: tile (tx, ty) of nodes per
  * workgroup; 0 keeps the default. tx is 64 (one wavefront per row); ty is
- * 2, 4, 8 or 16 in 2D (default 4 for DDCC_FP64, 8 otherwise) and 2 or 4
- * in 3D (default 4). Any other value returns DDCC_E_INVAL. Takes effect on
+ * 2, 4, 8 or 16 in 2D (default 4 for DDCC_FP64, 8 otherwise, and 2 or 4
+ * for boxes that leave the chip partly idle) and 2 or 4 in 3D (default 4). Any other value returns DDCC_E_INVAL. Takes effect on
  * the next ddcc_step; results do not depend on the tile. */
 int ddcc_set_tile(ddcc_ctx* ctx, int tx, int ty);
 

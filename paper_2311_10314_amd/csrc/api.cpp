@@ -340,7 +340,7 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
   b.outP = oP;
   if (c->p.dim == 2)
     return launch_2d<Pop, S, R>(c->p.nphase, mode, c->kd, k, b, c->tile_y,
-                                c->stream);
+                                c->cus, c->stream);
   return launch_3d<Pop, S, R>(c->p.nphase, c->p.lattice_f, mode, c->kd, k, b,
                               c->tile_x, c->tile_y, c->cus, c->stream);
 }
@@ -502,17 +502,17 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   c->nT = d * (d - 1) / 2;
   c->esz = p->precision == DDCC_FP64 ? 8 : 4;
   c->pesz = p->precision == DDCC_FP64 ? 8 : (p->precision == DDCC_FP32 ? 4 : 2);
-  // 2D: 64 x 4 tiles for float64 arithmetic (its registers allow three
-  // waves per SIMD, which 4-wave workgroups fill; 1-15 % faster than 64 x 8
-  // from 4096^2 down to 128^2), 64 x 8 for float; 3D: 64 x 4 columns.
-  c->tile_y = d == 2 ? (p->precision == DDCC_FP64 ? 4 : 8) : 4;
-  c->tile_x = 64;
   if (hipGetDevice(&c->device) != hipSuccess ||
       hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount,
                             c->device) != hipSuccess) {
     delete c;
     return DDCC_E_HIP;
   }
+  // 3D: 64 x 4 columns
+  c->tile_y = d == 2 ? default_tile_2d(p->nx, p->ny, p->precision == DDCC_FP64,
+                                       c->cus)
+                     : 4;
+  c->tile_x = 64;
   if (stream) {
     c->stream = static_cast<hipStream_t>(stream);
   } else {

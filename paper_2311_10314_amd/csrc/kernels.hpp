@@ -60,11 +60,15 @@ __device__ inline Pop narrow(R v, double& comp) {
 }
 
 // kd: the float64 constants (fields C, mu, psi, rest populations);
-// k: the same constants in the collision arithmetic type R.
+// k: the same constants in the collision arithmetic type R; cus: compute
+// units of the device.
 template <class Pop, class S, class R>
 hipError_t launch_2d(int nphase, int mode, const Coef<double>& kd,
-                     const Coef<R>& k, const Bufs<Pop, S>& b, int ty,
+                     const Coef<R>& k, const Bufs<Pop, S>& b, int ty, int cus,
                      hipStream_t st);
+
+// Default tile height of launch_2d for a box.
+int default_tile_2d(int nx, int ny, bool fp64, int cus);
 
 // lattice_f: the phase-set lattice id (D3Q15 or D3Q7 of lattice.hpp); cus:
 // compute units of the device.

@@ -269,7 +269,10 @@ struct Step2D {
 #pragma unroll
       for (int q = 0; q < N; ++q)
         if (q != j) {
-          const D cjq = (k.sigN[j] * ct[j] - k.sigN[q] * ct[q]) * k.inv_sig[j][q];
+          // which product of the difference is rounded is fixed here: left to
+          // the compiler it may differ between the kernels that share this
+          const D cjq = fma(-k.sigN[q], ct[q], k.sigN[j] * ct[j]) *
+                        k.inv_sig[j][q];
           acc += cjq * C[j] * C[q];
         }
       W[j] = acc;
@@ -293,8 +296,7 @@ struct Step2D {
     if constexpr (MODE != MODE_INIT && !PRE2) sm.T[my][mx] = R(ldp(b.TA, idx));
   }
 
-  __device__ static void run(const Coef<D>& kd, const Coef<R>& k,
-                             const Bufs<Pop, S>& b) {
+  __device__ static inline void tile_of(int& x0, int& y0) {
     // Tile order. Workgroup w is dispatched to XCD w % 8. The row-major tile
     // list is cut into spans of 8 chunks of CH full-width tile rows (64 node
     // rows), and inside a span each XCD takes one contiguous range, about one
@@ -302,22 +304,25 @@ struct Step2D {
     // below) then sit in one XCD's L2 instead of being fetched by two or
     // three, and the eight XCDs work on adjacent chunks, so the pages in use
     // stay few.
+    constexpr unsigned CH = TY >= 64 ? 1u : 64u / TY;
+    const unsigned gx = gridDim.x, total = gx * gridDim.y;
+    const unsigned lin = blockIdx.y * gx + blockIdx.x;
+    const unsigned span = 8u * CH * gx;
+    const unsigned base = lin / span * span;
+    const unsigned m = min(span, total - base);
+    const unsigned l = lin - base, q = m / 8u, r = m % 8u;
+    const unsigned xc = l % 8u, j = l / 8u;
+    const unsigned t = base + (xc < r ? xc * (q + 1u) + j
+                                      : r * (q + 1u) + (xc - r) * q + j);
+    x0 = int(t % gx) * TX;
+    y0 = int(t / gx) * TY;
+  }
+
+  __device__ static void run(const Coef<D>& kd, const Coef<R>& k,
+                             const Bufs<Pop, S>& b) {
     __shared__ Smem sm;
     int x0, y0;
-    {
-      constexpr unsigned CH = TY >= 64 ? 1u : 64u / TY;
-      const unsigned gx = gridDim.x, total = gx * gridDim.y;
-      const unsigned lin = blockIdx.y * gx + blockIdx.x;
-      const unsigned span = 8u * CH * gx;
-      const unsigned base = lin / span * span;
-      const unsigned m = min(span, total - base);
-      const unsigned l = lin - base, q = m / 8u, r = m % 8u;
-      const unsigned xc = l % 8u, j = l / 8u;
-      const unsigned t = base + (xc < r ? xc * (q + 1u) + j
-                                        : r * (q + 1u) + (xc - r) * q + j);
-      x0 = int(t % gx) * TX;
-      y0 = int(t / gx) * TY;
-    }
+    tile_of(x0, y0);
     if constexpr (MODE == MODE_STREAM) {
       body(sm, kd, k, b, Grid{k.nx, k.ny, k.n, 0u}, x0, y0);
       return;
@@ -411,6 +416,113 @@ struct Step2D {
                         &fown, &in3);
   }
 
+  // Phase-1 inputs of the C-region node (lx, ly).
+  struct In1 {
+    Pop f[N][Q - 1];
+    D f0[N];
+    S psi;
+  };
+  __device__ static inline void load1(const Bufs<Pop, S>& b, const Grid& gd,
+                                      int x0, int y0, int lx, int ly, In1& in) {
+    const int gx = wrap(x0 + lx - 2, gd.nx), gy = wrap(y0 + ly - 2, gd.ny);
+    const unsigned idx = gd.off + unsigned(gy * gd.nx + gx);
+    const Nbr nb = make_nbr(gx, gy, gd.nx, gd.ny, gd.off);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int p = 1; p < Q; ++p)
+        in.f[i][p - 1] = ldp(phase_plane(b.fA, i, p, Q, gd.n),
+                             nb.src(D2Q9::c[p].x, D2Q9::c[p].y));
+      in.f0[i] = ldp(b.f0A + (long long)(i) * gd.n, idx);
+    }
+    in.psi = ldp(b.psi, idx);
+  }
+
+  // Phase 1 from loaded inputs (the arithmetic of node1).
+  __device__ static inline void calc1(Smem& sm, const Coef<D>& k, const In1& in,
+                                      int lx, int ly, D* psiC_out) {
+    const D psi = D(in.psi);
+    D rho = D(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      R mv = R(0);
+#pragma unroll
+      for (int p = 1; p < Q; ++p) mv += R(in.f[i][p - 1]);
+      psiC_out[i] = in.f0[i] + D(mv);
+    }
+    D tot = D(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) tot += psiC_out[i];
+    const D inv = D(1) / (tot > k.psi_min ? tot : k.psi_min);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const D C = psiC_out[i] * inv;
+      sm.C[i][ly][lx] = C;
+      rho += k.rho[i] * C;
+    }
+    sm.psi[ly][lx] = psi;
+    sm.prho[ly][lx] = psi * rho;
+  }
+
+  // One tile by a wide workgroup of WT threads: NT for the tile's nodes, the
+  // rest for its halo, one node per thread and phase. For boxes that leave
+  // the chip partly idle, where a step lasts as long as one tile: the halo
+  // nodes run beside the tile's own instead of after them, every load of the
+  // step goes out at the start, and the box size is a kernel argument, so
+  // that a tile waits on memory once instead of five times. Same results bit
+  // for bit. us per step (same GPU), plain -> wide: 96 x 70 FP32 8.5 -> 6.6 and
+  // 128^2 FP64 9.9 -> 7.3 (64 x 2 tiles), 256^2 FP32 9.4 -> 8.0 (64 x 4). On
+  // fuller chips the threads that only serve the halo cost more than they
+  // save: 512^2 N = 3 FP32 22.8 -> 26.5, 256^2 FP64 (64 x 4, three boxes at
+  // once) 8.8 -> 10.4.
+  static constexpr int WT = NT + (RING1 + 63) / 64 * 64;
+  __device__ static inline void wide(Smem& sm, const Coef<D>& kd,
+                                     const Coef<R>& k, const Bufs<Pop, S>& b,
+                                     const Grid& gd, int x0, int y0) {
+    const int tid = threadIdx.x;
+    const bool inner = tid < NT;
+    const int tx = tid % TX, ty = tid / TX;
+    int lx = tx + 2, ly = ty + 2, mx = tx + 1, my = ty + 1;
+    bool on1 = true, on2 = true;
+    if (!inner) {
+      const int r = tid - NT;
+      on1 = r < RING1;
+      on2 = r < RING2;
+      ring1(on1 ? r : 0, lx, ly);
+      ring2(on2 ? r : 0, mx, my);
+    }
+    const bool own = inner && x0 + tx < gd.nx && y0 + ty < gd.ny;
+    In1 in1;
+    In3 in3;
+    S E[N], T = S(0);
+    if (on1) load1(b, gd, x0, y0, lx, ly, in1);
+    if (on2) {
+      const int gx = wrap(x0 + mx - 1, gd.nx), gy = wrap(y0 + my - 1, gd.ny);
+      const unsigned idx = gd.off + unsigned(gy * gd.nx + gx);
+#pragma unroll
+      for (int i = 0; i < N - 1; ++i) E[i] = ldp(b.wet + (long long)(i) * gd.n, idx);
+      T = ldp(b.TA, idx);
+    }
+    if (own) load3<false>(b, gd, x0, y0, tx, ty, in3);
+    D psiC[N], psimu_d[N];
+    if (on1) calc1(sm, kd, in1, lx, ly, psiC);
+    if (on2) sm.T[my][mx] = R(T);
+    __syncthreads();
+    if (on2) node2<true>(sm, kd, b, gd, x0, y0, mx, my, psimu_d, E);
+    __syncthreads();
+    if (own) {
+      Keep fown;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+#pragma unroll
+        for (int p = 1; p < Q; ++p) fown[i][p] = R(in1.f[i][p - 1]);
+        in3.f0[i] = in1.f0[i];
+      }
+      node3<true, true>(sm, kd, k, b, gd, x0, y0, tx, ty, psiC, psimu_d, &fown,
+                        &in3);
+    }
+  }
+
   // One TX x TY tile with its corner at (x0, y0) of box gd. Every thread of
   // the workgroup passes both barriers; there is no early return, so a
   // workgroup can process several tiles in a row.
@@ -454,6 +566,7 @@ struct Step2D {
     S hX[2 * N], hY[3], hP;
     D f0[N];
   };
+  template <bool F0 = true>
   __device__ static inline void load3(const Bufs<Pop, S>& b, const Grid& gd,
                                       int x0, int y0, int tx, int ty, In3& in) {
     if constexpr (MODE != MODE_INIT) {
@@ -469,8 +582,10 @@ struct Step2D {
 #pragma unroll
       for (int q = 0; q < 3; ++q) in.hY[q] = ldo<STREAM>(b.hist + (long long)(2 * N + q) * n, idx);
       in.hP = ldo<STREAM>(b.hist + (long long)(2 * N + 3) * n, idx);
+      if constexpr (F0) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) in.f0[i] = ldp(b.f0A + (long long)(i) * n, idx);
+        for (int i = 0; i < N; ++i) in.f0[i] = ldp(b.f0A + (long long)(i) * n, idx);
+      }
     }
   }
 
@@ -714,6 +829,15 @@ struct Step2D {
   }
 };
 
+// Whether a step in 64 x ty tiles takes wide workgroups (Step2D::wide): the
+// tiles fit the compute units, one each. 64 x 4 tiles only in float
+// arithmetic: the nine waves of a float64 one are all that its 156 registers
+// leave room for on a compute unit.
+bool wide_tiles(int nx, int ny, bool fp64, int ty, int cus) {
+  if (ty != 2 && !(ty == 4 && !fp64)) return false;
+  return (long long)((nx + TX - 1) / TX) * ((ny + ty - 1) / ty) <= cus;
+}
+
 // kd, k: the context's coefficients in device memory. Passed by value the
 // two structs (about 1.5 KB) overflow the scalar registers and spill into
 // VGPR lanes; read through __restrict__ pointers they are scalar loads where
@@ -725,13 +849,39 @@ __global__ __launch_bounds__(TX* TY) void k_step2d(
   Step2D<N, Pop, S, R, MODE, TY>::run(*kd, *k, b);
 }
 
+template <int N, class Pop, class S, class R, int MODE, int TY>
+__global__ __launch_bounds__((Step2D<N, Pop, S, R, MODE, TY>::WT)) void
+k_step2d_wide(const Coef<double>* __restrict__ kd,
+              const Coef<R>* __restrict__ k, Bufs<Pop, S> b, Grid gd) {
+  using T = Step2D<N, Pop, S, R, MODE, TY>;
+  __shared__ typename T::Smem sm;
+  int x0, y0;
+  T::tile_of(x0, y0);
+  T::wide(sm, *kd, *k, b, gd, x0, y0);
+}
+
 template <int N, class Pop, class S, class R, int MODE>
 hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
-                     const Bufs<Pop, S>& b, int ty, hipStream_t st) {
+                     const Bufs<Pop, S>& b, int ty, int cus, hipStream_t st) {
   (void)kd;
   const Coef<double>* dk = static_cast<const Coef<double>*>(b.coef_d);
   const Coef<R>* dr = static_cast<const Coef<R>*>(b.coef_r);
   if (!dk || !dr) return hipErrorInvalidValue;
+  if constexpr (MODE == MODE_STEP) {
+    if (wide_tiles(k.nx, k.ny, sizeof(R) == 8, ty, cus)) {
+      const Grid gd{k.nx, k.ny, k.n, 0u};
+      const dim3 g((k.nx + TX - 1) / TX, (k.ny + ty - 1) / ty);
+      if (ty == 2)
+        hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 2>), g,
+                           dim3(Step2D<N, Pop, S, R, MODE, 2>::WT), 0, st, dk,
+                           dr, b, gd);
+      else
+        hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 4>), g,
+                           dim3(Step2D<N, Pop, S, R, MODE, 4>::WT), 0, st, dk,
+                           dr, b, gd);
+      return hipGetLastError();
+    }
+  }
   switch (ty) {
     case 4: {
       dim3 g((k.nx + TX - 1) / TX, (k.ny + 3) / 4);
@@ -763,16 +913,16 @@ hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
 
 template <int N, class Pop, class S, class R>
 hipError_t launch_mode(int mode, const Coef<double>& kd, const Coef<R>& k,
-                       const Bufs<Pop, S>& b, int ty, hipStream_t st) {
+                       const Bufs<Pop, S>& b, int ty, int cus, hipStream_t st) {
   switch (mode) {
     case MODE_STEP:
-      return launch_ty<N, Pop, S, R, MODE_STEP>(kd, k, b, ty, st);
+      return launch_ty<N, Pop, S, R, MODE_STEP>(kd, k, b, ty, cus, st);
     case MODE_STREAM:
-      return launch_ty<N, Pop, S, R, MODE_STREAM>(kd, k, b, ty, st);
+      return launch_ty<N, Pop, S, R, MODE_STREAM>(kd, k, b, ty, cus, st);
     case MODE_INIT:
-      return launch_ty<N, Pop, S, R, MODE_INIT>(kd, k, b, ty, st);
+      return launch_ty<N, Pop, S, R, MODE_INIT>(kd, k, b, ty, cus, st);
     default:
-      return launch_ty<N, Pop, S, R, MODE_MOMENTS>(kd, k, b, ty, st);
+      return launch_ty<N, Pop, S, R, MODE_MOMENTS>(kd, k, b, ty, cus, st);
   }
 }
 
@@ -841,17 +991,29 @@ int batch_blocks_n() {
 
 }  // namespace
 
+// float64 arithmetic: 64 x 4 tiles (its registers allow three waves per SIMD,
+// which 4-wave workgroups fill; 1-15 % faster than 64 x 8 from 4096^2 down to
+// 128^2); float: 64 x 8. Boxes small enough for wide workgroups take the
+// lower tiles that those come in: 64 x 2 while they fill at most half the
+// chip, then 64 x 4 (96 x 70 FP32 6.6 against 6.9 us, 256^2 FP32 8.9 against
+// 8.0 us with 64 x 4).
+int default_tile_2d(int nx, int ny, bool fp64, int cus) {
+  if (wide_tiles(nx, ny, fp64, 2, fp64 ? cus : cus / 2)) return 2;
+  if (wide_tiles(nx, ny, fp64, 4, cus)) return 4;
+  return fp64 ? 4 : 8;
+}
+
 template <class Pop, class S, class R>
 hipError_t launch_2d(int nphase, int mode, const Coef<double>& kd,
-                     const Coef<R>& k, const Bufs<Pop, S>& b, int ty,
+                     const Coef<R>& k, const Bufs<Pop, S>& b, int ty, int cus,
                      hipStream_t st) {
   switch (nphase) {
     case 2:
-      return launch_mode<2, Pop, S, R>(mode, kd, k, b, ty, st);
+      return launch_mode<2, Pop, S, R>(mode, kd, k, b, ty, cus, st);
     case 3:
-      return launch_mode<3, Pop, S, R>(mode, kd, k, b, ty, st);
+      return launch_mode<3, Pop, S, R>(mode, kd, k, b, ty, cus, st);
     case 4:
-      return launch_mode<4, Pop, S, R>(mode, kd, k, b, ty, st);
+      return launch_mode<4, Pop, S, R>(mode, kd, k, b, ty, cus, st);
     default:
       return hipErrorInvalidValue;
   }
@@ -914,15 +1076,15 @@ DDCC_BATCH_INST(__bf16, float, float)
 
 template hipError_t launch_2d<double, double, double>(
     int, int, const Coef<double>&, const Coef<double>&,
-    const Bufs<double, double>&, int, hipStream_t);
+    const Bufs<double, double>&, int, int, hipStream_t);
 template hipError_t launch_2d<float, float, float>(
     int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<float, float>&, int, hipStream_t);
+    const Bufs<float, float>&, int, int, hipStream_t);
 template hipError_t launch_2d<_Float16, float, float>(
     int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<_Float16, float>&, int, hipStream_t);
+    const Bufs<_Float16, float>&, int, int, hipStream_t);
 template hipError_t launch_2d<__bf16, float, float>(
     int, int, const Coef<double>&, const Coef<float>&,
-    const Bufs<__bf16, float>&, int, hipStream_t);
+    const Bufs<__bf16, float>&, int, int, hipStream_t);
 
 }  // namespace ddcc

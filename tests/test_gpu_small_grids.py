@@ -1,0 +1,55 @@
+"""Launch shapes of boxes that leave the chip partly idle, against the oracle.
+
+2D boxes whose tiles fit the compute units run in wide workgroups (a thread
+per halo node): one-tile boxes, partial tiles in x and y, and the largest
+boxes of the 64 x 2 and 64 x 4 shapes. 3D boxes take shorter z columns: one
+plane per workgroup, a last column with fewer planes than the others, one
+tile. Bars: the method's own, FP64 1e-10 and FP32 1e-5 on C_i and u.
+"""
+import pytest
+
+from paper_2311_10314_amd import workloads as W
+from tests.helpers import oracle_run, rel_linf
+
+pytestmark = pytest.mark.gpu
+
+BAR = {"fp64": 1e-10, "fp32": 1e-5}
+
+
+def _check(wl, precision, steps, tile=0):
+    from paper_2311_10314_amd.ddcc import Sim
+    print(wl.shape, wl.nphase, precision, "tile", tile, flush=True)
+    sim = Sim.from_workload(wl, precision)
+    sim.set_tile(0, tile)
+    sim.step(steps)
+    C, u, _ = sim.read_moments()
+    sim.close()
+    o = oracle_run(wl, steps)
+    eC = max(rel_linf(C[i], o["C"][i]) for i in range(wl.nphase))
+    eu = rel_linf(u, o["u"])
+    print("C %.2e u %.2e" % (eC, eu), flush=True)
+    assert eC < BAR[precision] and eu < BAR[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N,shape", [(2, (1, 64)), (3, (3, 65)), (4, (5, 130)),
+                                     (2, (128, 128)), (3, (127, 127)),
+                                     (2, (256, 200)), (3, (253, 255))])
+def test_wide_workgroups(N, shape, precision):
+    _check(W.random_small(2, N, shape, seed=41), precision, 4)
+
+
+@pytest.mark.parametrize("tile", [2, 4])
+def test_wide_workgroups_by_tile(tile):
+    """Both heights of the wide shape on one box (64 x 4: float only)."""
+    _check(W.random_small(2, 2, (129, 129), seed=42), "fp32", 4, tile)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N,lattice,shape", [(2, "D3Q15", (5, 3, 20)),
+                                             (2, "D3Q15", (17, 30, 66)),
+                                             (3, "D3Q7", (7, 50, 100))])
+def test_short_columns(N, lattice, shape, precision):
+    prm = {"d0": 0.3} if lattice == "D3Q7" else {}
+    _check(W.random_small(3, N, shape, seed=43, lattice_f=lattice, **prm),
+           precision, 3)
