@@ -380,7 +380,7 @@ void release(ddcc_ctx* c) {
   void* ptrs[] = {c->f[0],  c->f[1],   c->f0[0],    c->f0[1], c->g[0],
                   c->g[1],  c->T[0],   c->T[1],     c->hist,  c->psi,
                   c->wet,   c->staging, c->partial, c->bad,  c->work,
-                  c->diag_partial, c->diag_bad, c->diag_first,
+                  c->diag_partial, c->diag_first,
                   c->dkd,   c->dkf,    c->geo64};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -388,24 +388,26 @@ void release(ddcc_ctx* c) {
 }
 
 // Launch the per-phase population sums of the current state into
-// partial[block * N + i] with non-finite flags bad[block].
-hipError_t mass_into(ddcc_ctx* c, double* partial, int* bad) {
+// partial[block * N + i] with non-finite flags bad[block]; *first = t at the
+// first non-finite population if first is not NULL (launch_mass).
+hipError_t mass_into(ddcc_ctx* c, double* partial, int* bad,
+                     long long* first = nullptr, long long t = 0) {
   const int N = c->p.nphase;
   const void* f = c->f[c->cur];
   const double* f0 = c->f0[c->cur];
+  const auto go = [&](const auto* pops) {
+    return launch_mass(f0, pops, N, c->Qf, c->n, c->n, partial, bad,
+                       c->mass_blocks, c->stream, first, t);
+  };
   switch (c->p.precision) {
     case DDCC_FP64:
-      return launch_mass(f0, static_cast<const double*>(f), N, c->Qf, c->n,
-                         c->n, partial, bad, c->mass_blocks, c->stream);
+      return go(static_cast<const double*>(f));
     case DDCC_FP16:
-      return launch_mass(f0, static_cast<const _Float16*>(f), N, c->Qf, c->n,
-                         c->n, partial, bad, c->mass_blocks, c->stream);
+      return go(static_cast<const _Float16*>(f));
     case DDCC_BF16:
-      return launch_mass(f0, static_cast<const __bf16*>(f), N, c->Qf, c->n,
-                         c->n, partial, bad, c->mass_blocks, c->stream);
+      return go(static_cast<const __bf16*>(f));
     default:
-      return launch_mass(f0, static_cast<const float*>(f), N, c->Qf, c->n,
-                         c->n, partial, bad, c->mass_blocks, c->stream);
+      return go(static_cast<const float*>(f));
   }
 }
 
@@ -736,10 +738,8 @@ int ddcc_step(ddcc_ctx* c, int64_t nsteps) {
     c->cur ^= 1;
     ++c->t;
     if (c->diag_every > 0 && c->t % c->diag_every == 0) {
-      e = mass_into(c, c->diag_partial, c->diag_bad);
-      if (e == hipSuccess)
-        e = launch_sticky(c->diag_bad, c->mass_blocks, c->diag_first,
-                          (long long)c->t, c->stream);
+      e = mass_into(c, c->diag_partial, nullptr, c->diag_first,
+                    (long long)c->t);
       if (e != hipSuccess) return hip_fail(c, e, "diagnostics");
       c->diag_t = c->t;
     }
@@ -959,8 +959,6 @@ int ddcc_set_diagnostics(ddcc_ctx* c, int every) {
     const int N = c->p.nphase;
     HIPCHK(c, hipMalloc(&c->diag_partial,
                         (size_t)c->mass_blocks * N * sizeof(double)),
-           "hipMalloc diagnostics");
-    HIPCHK(c, hipMalloc(&c->diag_bad, (size_t)c->mass_blocks * sizeof(int)),
            "hipMalloc diagnostics");
     HIPCHK(c, hipMalloc(&c->diag_first, sizeof(long long)), "hipMalloc diagnostics");
   }

@@ -49,7 +49,6 @@ struct ddcc_ctx {
   int diag_every = 0;
   int64_t diag_t = -1;          // time level of the last check
   double* diag_partial = nullptr;
-  int* diag_bad = nullptr;
   long long* diag_first = nullptr;  // first level that saw a non-finite value
   std::string err;
   Coef<double> kd{};

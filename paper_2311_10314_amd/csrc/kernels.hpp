@@ -124,11 +124,14 @@ hipError_t launch_fill_u32(unsigned* dst, unsigned v, long long count,
 
 // Per-phase sums of all populations (rest plane f0 [N][stride_n] plus
 // the moving planes of f [N][Q-1][stride_n], nodes [0, n) of each plane) into
-// partial[block * N + i], plus a non-finite flag per block in bad[block].
+// partial[block * N + i], plus a non-finite flag per block in bad[block] (if
+// not NULL). first (may be NULL): *first = t if any population was not finite
+// and *first is -1.
 template <class Pop>
 hipError_t launch_mass(const double* f0, const Pop* f, int nphase, int Q,
                        long long n, long long stride_n, double* partial,
-                       int* bad, int nblocks, hipStream_t st);
+                       int* bad, int nblocks, hipStream_t st,
+                       long long* first = nullptr, long long t = 0);
 
 // Blocks of the mass kernel whose partials fit the static workspace of the
 // allocation-free mass check (the library never launches more).
@@ -140,14 +143,10 @@ hipError_t scratch_address(int device, void** ptr, size_t* bytes);
 
 // out[i] = sum over blocks b in order of partial[b * N + i] (i < N, float64,
 // as ddcc_mass sums them on the host); *nonfinite = OR of bad[0 .. nb) when
-// nonfinite is not NULL. One wave.
+// nonfinite is not NULL. One workgroup.
 hipError_t launch_mass_finish(const double* partial, const int* bad, int nb,
                               int N, double* out, int* nonfinite,
                               hipStream_t st);
-
-// *first = t if any of bad[0 .. nb) is set and *first < 0 (one wave).
-hipError_t launch_sticky(const int* bad, int nb, long long* first,
-                         long long t, hipStream_t st);
 
 // dst[i] = S(src[i]) for i < count.
 template <class S>

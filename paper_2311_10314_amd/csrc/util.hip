@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -25,62 +26,67 @@ constexpr int kWaves = kMassThreads / 64;
 
 // Per-phase population sums in float64: every thread accumulates a strided
 // slice, wavefronts reduce with cross-lane shuffles, the four waves of the
-// block through LDS; one partial per block and phase (summed on the host in
-// block order, so the result is deterministic).
-template <class S>
-__global__ __launch_bounds__(kMassThreads) void k_mass(const double* f0,
-                                                       const S* f, int N, int Q,
-                                                       long long n,
-                                                       long long stride_n,
-                                                       double* partial,
-                                                       int* bad) {
-  double acc[kMaxN] = {0.0, 0.0, 0.0, 0.0};
+// block through LDS; one partial per block and phase (summed in block order
+// by the host or k_mass_finish, so the result is deterministic). bad (may be
+// NULL): a non-finite flag per block; first (may be NULL): *first = t if a
+// population was not finite and *first is still -1 (the time level of the
+// first check that saw one). Bound by memory: N and Q are template
+// parameters so that a node's N Q loads are in flight together (512^2 N = 3
+// FP32: 12.4 us, and 4.6 us for a kernel of its own that gathered the flags,
+// -> 7.7 us; with run-time loops each load waited for the one before).
+template <int N, int Q, class S>
+__global__ __launch_bounds__(kMassThreads) void k_mass(
+    const double* __restrict__ f0, const S* __restrict__ f, long long n,
+    long long stride_n, double* __restrict__ partial, int* __restrict__ bad,
+    unsigned long long* first, long long t) {
+  double acc[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = 0.0;
   int nonfinite = 0;
   const long long stride = (long long)gridDim.x * kMassThreads;
   for (long long x = (long long)blockIdx.x * kMassThreads + threadIdx.x; x < n;
        x += stride) {
+    double s[N];
+    S v[N][Q - 1];
+#pragma unroll
     for (int i = 0; i < N; ++i) {
-      double s = f0[(long long)i * stride_n + x];
-      for (int p = 1; p < Q; ++p) {
-        const double v = double(phase_plane(f, i, p, Q, stride_n)[x]);
-        s += v;
-      }
-      if (!isfinite(s)) nonfinite = 1;
-      acc[i] += s;
+      s[i] = f0[(long long)i * stride_n + x];
+#pragma unroll
+      for (int p = 1; p < Q; ++p) v[i][p - 1] = phase_plane(f, i, p, Q, stride_n)[x];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int p = 1; p < Q; ++p) s[i] += double(v[i][p - 1]);
+      if (!isfinite(s[i])) nonfinite = 1;
+      acc[i] += s[i];
     }
   }
-  for (int i = 0; i < kMaxN; ++i)
+#pragma unroll
+  for (int i = 0; i < N; ++i)
     for (int off = 32; off > 0; off >>= 1) acc[i] += __shfl_xor(acc[i], off);
   for (int off = 32; off > 0; off >>= 1) nonfinite |= __shfl_xor(nonfinite, off);
-  __shared__ double red[kWaves][kMaxN];
+  __shared__ double red[kWaves][N];
   __shared__ int redbad[kWaves];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   if (lane == 0) {
-    for (int i = 0; i < kMaxN; ++i) red[wave][i] = acc[i];
+#pragma unroll
+    for (int i = 0; i < N; ++i) red[wave][i] = acc[i];
     redbad[wave] = nonfinite;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     int b = 0;
     for (int w = 0; w < kWaves; ++w) b |= redbad[w];
+#pragma unroll
     for (int i = 0; i < N; ++i) {
       double s = 0.0;
       for (int w = 0; w < kWaves; ++w) s += red[w][i];
       partial[(long long)blockIdx.x * N + i] = s;
     }
-    bad[blockIdx.x] = b;
+    if (bad) bad[blockIdx.x] = b;
+    if (b && first) atomicCAS(first, ~0ull, (unsigned long long)t);
   }
-}
-
-// One wave: if any of the nb block flags is set and *first is still
-// negative, *first = t (the time level of the first check that saw a
-// non-finite population).
-__global__ __launch_bounds__(64) void k_sticky(const int* bad, int nb,
-                                               long long* first, long long t) {
-  int b = 0;
-  for (int i = threadIdx.x; i < nb; i += 64) b |= bad[i];
-  for (int off = 32; off > 0; off >>= 1) b |= __shfl_xor(b, off);
-  if (threadIdx.x == 0 && b && *first < 0) *first = t;
 }
 
 template <class S>
@@ -141,22 +147,40 @@ __global__ void k_wet_field(const double* psik, const double* ctk, int K,
 
 // Per-phase totals from the per-block partials, summed in block order by
 // one lane per phase (the order and arithmetic of ddcc_mass's host sum, so
-// the two agree bit for bit), and the OR of the block flags.
-__global__ __launch_bounds__(64) void k_mass_finish(const double* partial,
-                                                    const int* bad, int nb,
-                                                    int N, double* out,
-                                                    int* nonfinite) {
+// the two agree bit for bit), and the OR of the block flags. The order makes
+// a chain of nb additions; the partials are staged in LDS so that the chain
+// waits for additions alone (1024 blocks, N = 3: 104 -> 17 us).
+constexpr int kFinishThreads = 256;
+__global__ __launch_bounds__(kFinishThreads) void k_mass_finish(
+    const double* __restrict__ partial, const int* __restrict__ bad, int nb,
+    int N, double* out, int* nonfinite) {
+  __shared__ double part[kScratchBlocks * kMaxN];
+  __shared__ int flag[kFinishThreads / 64];
+  for (int q = threadIdx.x; q < nb * N; q += kFinishThreads) part[q] = partial[q];
+  int f = 0;
+  if (nonfinite)
+    for (int b = threadIdx.x; b < nb; b += kFinishThreads) f |= bad[b];
+  for (int off = 32; off > 0; off >>= 1) f |= __shfl_xor(f, off);
+  if (threadIdx.x % 64 == 0) flag[threadIdx.x / 64] = f;
+  __syncthreads();
   const int i = int(threadIdx.x);
   if (i < N) {
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[(long long)b * N + i];
+    int b = 0;
+    for (; b + 32 <= nb; b += 32) {  // 32 LDS reads in flight, then 32 adds
+      double v[32];
+#pragma unroll
+      for (int q = 0; q < 32; ++q) v[q] = part[(b + q) * N + i];
+#pragma unroll
+      for (int q = 0; q < 32; ++q) s += v[q];
+    }
+    for (; b < nb; ++b) s += part[b * N + i];
     out[i] = s;
   }
-  if (nonfinite) {
-    int f = 0;
-    for (int b = i; b < nb; b += 64) f |= bad[b];
-    for (int off = 32; off > 0; off >>= 1) f |= __shfl_xor(f, off);
-    if (i == 0) *nonfinite = f;
+  if (nonfinite && i == 0) {
+    int any = 0;
+    for (int w = 0; w < kFinishThreads / 64; ++w) any |= flag[w];
+    *nonfinite = any;
   }
 }
 
@@ -193,8 +217,10 @@ hipError_t scratch_address(int device, void** ptr, size_t* bytes) {
 hipError_t launch_mass_finish(const double* partial, const int* bad, int nb,
                               int N, double* out, int* nonfinite,
                               hipStream_t st) {
-  if (nb < 1 || N < 1 || N > kMaxN || !out) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_mass_finish, dim3(1), dim3(64), 0, st, partial, bad,
+  if (nb < 1 || nb > kScratchBlocks || N < 1 || N > kMaxN || !out ||
+      (nonfinite && !bad))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_mass_finish, dim3(1), dim3(kFinishThreads), 0, st, partial, bad,
                      nb, N, out, nonfinite);
   return hipGetLastError();
 }
@@ -220,12 +246,6 @@ template hipError_t launch_wet_field<float>(const double*, const double*, int,
                                             int, int, int, int, float*, float*,
                                             long long, long long, hipStream_t);
 
-hipError_t launch_sticky(const int* bad, int nb, long long* first,
-                         long long t, hipStream_t st) {
-  hipLaunchKernelGGL(k_sticky, dim3(1), dim3(64), 0, st, bad, nb, first, t);
-  return hipGetLastError();
-}
-
 hipError_t launch_fill_u32(unsigned* dst, unsigned v, long long count,
                            hipStream_t st) {
   if (count <= 0) return hipSuccess;
@@ -237,10 +257,40 @@ hipError_t launch_fill_u32(unsigned* dst, unsigned v, long long count,
 template <class S>
 hipError_t launch_mass(const double* f0, const S* f, int nphase, int Q,
                        long long n, long long stride_n, double* partial,
-                       int* bad, int nblocks, hipStream_t st) {
-  hipLaunchKernelGGL((k_mass<S>), dim3(nblocks), dim3(kMassThreads), 0, st, f0,
-                     f, nphase, Q, n, stride_n, partial, bad);
-  return hipGetLastError();
+                       int* bad, int nblocks, hipStream_t st, long long* first,
+                       long long t) {
+  auto go = [&](auto nc, auto qc) {
+    constexpr int N = decltype(nc)::value, QC = decltype(qc)::value;
+    hipLaunchKernelGGL((k_mass<N, QC, S>), dim3(nblocks), dim3(kMassThreads),
+                       0, st, f0, f, n, stride_n, partial, bad,
+                       reinterpret_cast<unsigned long long*>(first), t);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  const integral_constant<int, 2> n2{};
+  const integral_constant<int, 3> n3{};
+  switch (Q) {
+    case 9: {
+      const auto q = integral_constant<int, 9>();
+      if (nphase == 2) return go(n2, q);
+      if (nphase == 3) return go(n3, q);
+      if (nphase == 4) return go(integral_constant<int, 4>(), q);
+      break;
+    }
+    case 7: {
+      const auto q = integral_constant<int, 7>();
+      if (nphase == 2) return go(n2, q);
+      if (nphase == 3) return go(n3, q);
+      break;
+    }
+    case 15: {
+      const auto q = integral_constant<int, 15>();
+      if (nphase == 2) return go(n2, q);
+      if (nphase == 3) return go(n3, q);
+      break;
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 template <class S>
@@ -255,17 +305,21 @@ hipError_t launch_convert(const double* src, S* dst, long long count,
 }
 
 template hipError_t launch_mass<double>(const double*, const double*, int, int,
-                                         long long, long long, double*,
-                                         int*, int, hipStream_t);
+                                         long long, long long, double*, int*,
+                                         int, hipStream_t, long long*,
+                                         long long);
 template hipError_t launch_mass<float>(const double*, const float*, int, int,
-                                         long long, long long, double*,
-                                         int*, int, hipStream_t);
+                                         long long, long long, double*, int*,
+                                         int, hipStream_t, long long*,
+                                         long long);
 template hipError_t launch_mass<_Float16>(const double*, const _Float16*, int, int,
-                                         long long, long long, double*,
-                                         int*, int, hipStream_t);
+                                         long long, long long, double*, int*,
+                                         int, hipStream_t, long long*,
+                                         long long);
 template hipError_t launch_mass<__bf16>(const double*, const __bf16*, int, int,
-                                         long long, long long, double*,
-                                         int*, int, hipStream_t);
+                                         long long, long long, double*, int*,
+                                         int, hipStream_t, long long*,
+                                         long long);
 template hipError_t launch_convert<double>(const double*, double*, long long,
                                            hipStream_t);
 template hipError_t launch_convert<float>(const double*, float*, long long,
