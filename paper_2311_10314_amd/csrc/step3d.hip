@@ -16,7 +16,7 @@
 //             post-collision populations written at the node (pull
 //             streaming).
 // k_frac3d runs one node per thread. k_mu3d and k_step3d give each
-// workgroup a 64 x TY column of nodes over zb planes and march it in z with
+// workgroup a TX x TY column of nodes over zb planes and march it in z with
 // three planes of their stencil fields (C_j, psi; and mu_i for the step) in
 // an LDS ring, so each value is fetched once per tile instead of once per
 // neighbour. The C and mu fields (in the field type: float64 for FP64
@@ -55,7 +55,6 @@ bool have_3d() { return true; }
 
 namespace {
 
-constexpr int TX = 64;
 using G19 = D3Q19;
 
 // Fixed isotropic stencil: D3Q19 weights at d0 = 1/3 (1/18 faces, 1/36
@@ -173,7 +172,7 @@ __device__ inline Star<T> gather(const S* plane, const Nbr3& nb) {
 // count is a multiple of 8), so the rows shared by neighbouring tiles of a
 // plane, and of the planes above and below, stay in one L2 (1.4-2.4 %
 // faster at 256^3, measured).
-template <int TY>
+template <int TX, int TY>
 __device__ inline bool node_of(const int nx, const int ny, int& x, int& y,
                                int& z) {
   z = int(blockIdx.z);
@@ -199,13 +198,14 @@ __device__ inline S* work_field(double* p) {
 }
 
 // ---- k_frac3d -------------------------------------------------------------
-template <int N, class LF, class Pop, class S, class R, int MODE, int TY>
+template <int N, class LF, class Pop, class S, class R, int MODE, int TX,
+          int TY>
 __global__ __launch_bounds__(TX* TY) void k_frac3d(Coef<double> k,
                                                     Bufs<Pop, S> b) {
   using D = double;
   constexpr int QF = LF::Q;
   int x, y, z;
-  if (!node_of<TY>(k.nx, k.ny, x, y, z)) return;
+  if (!node_of<TX, TY>(k.nx, k.ny, x, y, z)) return;
   const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz);
   const unsigned idx = nb.at(0, 0, 0);
   D psiC[N];
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(TX* TY) void k_frac3d(Coef<double> k,
 // ones (planes_per_group).
 constexpr int ZB = 8;
 
-template <int N, class Pop, class S, int TY, bool NT>
+template <int N, class Pop, class S, int TX, int TY, bool NT>
 __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b, int zb) {
   // arithmetic in the field type: float64 in FP64 contexts, float32 otherwise
   using D = std::conditional_t<std::is_same_v<S, double>, double, float>;
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b,
 // node's stencils of these fields read LDS, the rest of its inputs come from
 // global memory (256^3 step: FP32 3.17 -> 2.99 ms, FP64 5.52 -> 5.05 ms;
 // the 16-bit storages 2-6 % slower than with the gathers from L2).
-template <int N, int TY>
+template <int N, int TX, int TY>
 struct StepPlane {
   double c[N][TY + 2][TX + 2];
   double m[N][TY + 2][TX + 2];
@@ -489,14 +489,14 @@ __device__ inline void fetch_node(const Bufs<Pop, S>& b, long long n, int nx,
 }
 
 template <int N, class LF, class LG, class Pop, class S, class R, int MODE,
-          int TY, bool PRE, class PF>
+          int TX, int TY, bool PRE, class PF>
 __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
                                    const Bufs<Pop, S>& b, int x, int y, int z,
-                                   const StepPlane<N, TY>* const* pz, int lx,
+                                   const StepPlane<N, TX, TY>* const* pz, int lx,
                                    int ly, const NodeIn<N, LF, LG, Pop, S>& in,
                                    PF prefetch) {
   using D = double;
-  using Pl = StepPlane<N, TY>;
+  using Pl = StepPlane<N, TX, TY>;
   constexpr int QF = LF::Q, QG = LG::Q;
   constexpr bool NT = MODE == MODE_STREAM;  // streaming stores
   const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz);
@@ -805,18 +805,18 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
 // coefficients came as arguments (at two, FP32 was 17 % slower); with the
 // coefficient table two is the faster cap (same GPU, 256^3 per step: FP32
 // 2.95 -> 2.86 ms, FP16 2.68 -> 1.98 ms, BF16 unchanged).
-template <int N, int TY>
+template <int N, int TX, int TY>
 constexpr int step3d_waves() {
-  constexpr int wgs = int((160u * 1024u) / (3u * sizeof(StepPlane<N, TY>)));
-  constexpr int lds_waves = (wgs * TY + 3) / 4;
+  constexpr int wgs = int((160u * 1024u) / (3u * sizeof(StepPlane<N, TX, TY>)));
+  constexpr int lds_waves = (wgs * (TX * TY / 64) + 3) / 4;
   constexpr int cap = 2;
   return lds_waves < 1 ? 1 : (lds_waves < cap ? lds_waves : cap);
 }
 
 template <int N, class LF, class LG, class Pop, class S, class R, int MODE,
-          int TY>
+          int TX, int TY>
 __global__ __launch_bounds__(TX* TY)
-__attribute__((amdgpu_waves_per_eu(step3d_waves<N, TY>())))
+__attribute__((amdgpu_waves_per_eu(step3d_waves<N, TX, TY>())))
 void k_step3d(Coef<double> kda, Coef<R> ka,
               const Coef<double>* __restrict__ kdp,
               const Coef<R>* __restrict__ kp, Bufs<Pop, S> b, int zb) {
@@ -831,7 +831,7 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
                          std::is_same_v<Pop, _Float16>;
   const Coef<double>& kd = TABLE ? *kdp : kda;
   const Coef<R>& k = TABLE ? *kp : ka;
-  using Pl = StepPlane<N, TY>;
+  using Pl = StepPlane<N, TX, TY>;
   constexpr int HX = TX + 2, HY = TY + 2, HN = HX * HY;
   __shared__ Pl ring[3];
   const int nx = k.nx, ny = k.ny, nz = k.nz;
@@ -884,8 +884,12 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
   // to 165 VGPRs runs three waves per SIMD and drops to two with it (FP16
   // 1.655 -> 1.772 ms, BF16 1.696 -> 1.807 ms). FP64 (253 VGPRs without it)
   // has no room.
+  // The 16-bit storages take it with three phases, whose LDS ring leaves two
+  // waves per SIMD either way (130 x 75 x 101 D3Q7 FP16 323 -> 217 us).
   using In = NodeIn<N, LF, LG, Pop, S>;
-  constexpr bool PF = std::is_same_v<Pop, float> && MODE != MODE_INIT;
+  constexpr bool PF =
+      (std::is_same_v<Pop, float> || (sizeof(Pop) == 2 && N == 3)) &&
+      MODE != MODE_INIT;
   constexpr bool RF = PF;
   In cur;
   if constexpr (PF)
@@ -944,14 +948,14 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
     if (own) {
       const Pl* pz[3] = {&ring[(z + 2) % 3], &ring[z % 3], &ring[(z + 1) % 3]};
       if constexpr (PF) {
-        step3d_node<N, LF, LG, Pop, S, R, MODE, TY, true>(
+        step3d_node<N, LF, LG, Pop, S, R, MODE, TX, TY, true>(
             kd, k, b, x, y, z, pz, tx + 1, ty + 1, cur, [&] {
               if (more)
                 fetch_node<N, LF, LG, Pop, S, MODE>(b, k.n, nx, ny, nz, x, y,
                                                     z + 1, cur);
             });
       } else {
-        step3d_node<N, LF, LG, Pop, S, R, MODE, TY, false>(
+        step3d_node<N, LF, LG, Pop, S, R, MODE, TX, TY, false>(
             kd, k, b, x, y, z, pz, tx + 1, ty + 1, cur, [] {});
       }
     }
@@ -1002,15 +1006,16 @@ int groups_per_cu(K* kernel, int threads) {
   return per_cu < 1 ? 1 : per_cu;
 }
 
-template <int N, class LF, class Pop, class S, class R, int MODE, int TY>
+template <int N, class LF, class Pop, class S, class R, int MODE, int TX,
+          int TY>
 hipError_t launch_3(const Coef<double>& kd, const Coef<R>& k,
                     const Bufs<Pop, S>& b, int cus, hipStream_t st) {
   if (!b.coef_d || !b.coef_r) return hipErrorInvalidValue;
   const dim3 g((k.nx + TX - 1) / TX, (k.ny + TY - 1) / TY, k.nz);
   const dim3 blk(TX * TY);
-  constexpr auto* frac = &k_frac3d<N, LF, Pop, S, R, MODE, TY>;
-  constexpr auto* mu = &k_mu3d<N, Pop, S, TY, MODE == MODE_STREAM>;
-  constexpr auto* step = &k_step3d<N, LF, D3Q19, Pop, S, R, MODE, TY>;
+  constexpr auto* frac = &k_frac3d<N, LF, Pop, S, R, MODE, TX, TY>;
+  constexpr auto* mu = &k_mu3d<N, Pop, S, TX, TY, MODE == MODE_STREAM>;
+  constexpr auto* step = &k_step3d<N, LF, D3Q19, Pop, S, R, MODE, TX, TY>;
   // constants of the code object, looked up once
   static const int mu_per_cu = groups_per_cu(mu, TX * TY);
   static const int step_per_cu = groups_per_cu(step, TX * TY);
@@ -1031,16 +1036,31 @@ hipError_t launch_3(const Coef<double>& kd, const Coef<R>& k,
   return hipGetLastError();
 }
 
-template <int N, class Pop, class S, class R, int MODE>
-hipError_t launch_ty3(int lattice_f, const Coef<double>& kd, const Coef<R>& k,
+template <int N, class LF, class Pop, class S, class R, int MODE>
+hipError_t launch_ty3(const Coef<double>& kd, const Coef<R>& k,
                       const Bufs<Pop, S>& b, int ty, int cus,
                       hipStream_t st) {
-  if (lattice_f == D3Q7::ID) {
-    if (ty == 2) return launch_3<N, D3Q7, Pop, S, R, MODE, 2>(kd, k, b, cus, st);
-    return launch_3<N, D3Q7, Pop, S, R, MODE, 4>(kd, k, b, cus, st);
+  if (ty == 2)
+    return launch_3<N, LF, Pop, S, R, MODE, 64, 2>(kd, k, b, cus, st);
+  // Boxes at most 32 nodes wide would leave half of every 64-node row idle:
+  // 32 x 8 tiles there (same GPU, 24 x 150 x 100 FP32 96 -> 67 us per step).
+  // From 33 nodes on the rows are better kept long, even where 32 x 8 tiles
+  // have fewer idle nodes: 130 x 75 x 101 N = 3 D3Q7 FP32 248 -> 310 us, 80 x 90
+  // x 60 FP32 102 -> 103, 40 x 100 x 150 N = 3 FP64 318 -> 360.
+  if constexpr (MODE == MODE_STEP || MODE == MODE_STREAM) {
+    if (k.nx <= 32)
+      return launch_3<N, LF, Pop, S, R, MODE, 32, 8>(kd, k, b, cus, st);
   }
-  if (ty == 2) return launch_3<N, D3Q15, Pop, S, R, MODE, 2>(kd, k, b, cus, st);
-  return launch_3<N, D3Q15, Pop, S, R, MODE, 4>(kd, k, b, cus, st);
+  return launch_3<N, LF, Pop, S, R, MODE, 64, 4>(kd, k, b, cus, st);
+}
+
+template <int N, class Pop, class S, class R, int MODE>
+hipError_t launch_lat3(int lattice_f, const Coef<double>& kd,
+                       const Coef<R>& k, const Bufs<Pop, S>& b, int ty,
+                       int cus, hipStream_t st) {
+  if (lattice_f == D3Q7::ID)
+    return launch_ty3<N, D3Q7, Pop, S, R, MODE>(kd, k, b, ty, cus, st);
+  return launch_ty3<N, D3Q15, Pop, S, R, MODE>(kd, k, b, ty, cus, st);
 }
 
 template <int N, class Pop, class S, class R>
@@ -1049,17 +1069,17 @@ hipError_t launch_mode3(int mode, int lattice_f, const Coef<double>& kd,
                         int cus, hipStream_t st) {
   switch (mode) {
     case MODE_STEP:
-      return launch_ty3<N, Pop, S, R, MODE_STEP>(lattice_f, kd, k, b, ty, cus,
-                                                   st);
+      return launch_lat3<N, Pop, S, R, MODE_STEP>(lattice_f, kd, k, b, ty, cus,
+                                                    st);
     case MODE_STREAM:
-      return launch_ty3<N, Pop, S, R, MODE_STREAM>(lattice_f, kd, k, b, ty, cus,
-                                                   st);
+      return launch_lat3<N, Pop, S, R, MODE_STREAM>(lattice_f, kd, k, b, ty, cus,
+                                                    st);
     case MODE_INIT:
-      return launch_ty3<N, Pop, S, R, MODE_INIT>(lattice_f, kd, k, b, ty, cus,
-                                                   st);
+      return launch_lat3<N, Pop, S, R, MODE_INIT>(lattice_f, kd, k, b, ty, cus,
+                                                    st);
     default:
-      return launch_ty3<N, Pop, S, R, MODE_MOMENTS>(lattice_f, kd, k, b, ty, cus,
-                                                   st);
+      return launch_lat3<N, Pop, S, R, MODE_MOMENTS>(lattice_f, kd, k, b, ty, cus,
+                                                    st);
   }
 }
 

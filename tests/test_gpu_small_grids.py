@@ -4,7 +4,9 @@
 per halo node): one-tile boxes, partial tiles in x and y, and the largest
 boxes of the 64 x 2 and 64 x 4 shapes. 3D boxes take shorter z columns: one
 plane per workgroup, a last column with fewer planes than the others, one
-tile. Bars: the method's own, FP64 1e-10 and FP32 1e-5 on C_i and u.
+tile; boxes at most 32 nodes wide 32 x 8 tiles. Bars: the method's own, FP64
+1e-10 and FP32 1e-5 on C_i and u; FP16 storage (three phases: the plane
+pipeline) as in test_gpu_halfstore, C 10 u_s and u 50 u_s with u_s = 2^-11.
 """
 import pytest
 
@@ -13,7 +15,8 @@ from tests.helpers import oracle_run, rel_linf
 
 pytestmark = pytest.mark.gpu
 
-BAR = {"fp64": 1e-10, "fp32": 1e-5}
+BAR = {"fp64": (1e-10, 1e-10), "fp32": (1e-5, 1e-5),
+       "fp16": (10 * 2.0 ** -11, 50 * 2.0 ** -11)}
 
 
 def _check(wl, precision, steps, tile=0):
@@ -28,7 +31,7 @@ def _check(wl, precision, steps, tile=0):
     eC = max(rel_linf(C[i], o["C"][i]) for i in range(wl.nphase))
     eu = rel_linf(u, o["u"])
     print("C %.2e u %.2e" % (eC, eu), flush=True)
-    assert eC < BAR[precision] and eu < BAR[precision]
+    assert eC < BAR[precision][0] and eu < BAR[precision][1]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
@@ -48,8 +51,17 @@ def test_wide_workgroups_by_tile(tile):
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("N,lattice,shape", [(2, "D3Q15", (5, 3, 20)),
                                              (2, "D3Q15", (17, 30, 66)),
-                                             (3, "D3Q7", (7, 50, 100))])
+                                             (3, "D3Q7", (7, 50, 100)),
+                                             (2, "D3Q15", (9, 17, 32)),
+                                             (3, "D3Q15", (10, 15, 33))])
 def test_short_columns(N, lattice, shape, precision):
     prm = {"d0": 0.3} if lattice == "D3Q7" else {}
     _check(W.random_small(3, N, shape, seed=43, lattice_f=lattice, **prm),
            precision, 3)
+
+
+@pytest.mark.parametrize("lattice", ["D3Q15", "D3Q7"])
+def test_half_storage_three_phases(lattice):
+    prm = {"d0": 0.3} if lattice == "D3Q7" else {}
+    _check(W.random_small(3, 3, (11, 22, 70), seed=44, lattice_f=lattice,
+                          **prm), "fp16", 3)
