@@ -38,12 +38,14 @@ template <int N> __host__ __device__ constexpr int adj_C() { return 4 * N + 4; }
 template <int N> __host__ __device__ constexpr int adj_psimu() { return 5 * N + 4; }
 template <int N> __host__ __device__ constexpr int adj_psiC() { return 6 * N + 4; }
 template <int N> __host__ __device__ constexpr int adj_psirho() { return 7 * N + 4; }
-template <int N> __host__ __device__ constexpr int adj_L() { return 7 * N + 5; }
-__host__ __device__ constexpr int adj_planes(int N) { return 8 * N + 5; }
+__host__ __device__ constexpr int adj_planes(int N) { return 7 * N + 5; }
 
 // Adjoint state (float64, R) and the accumulated gradients.
 //   lfB/lgB/lTB: adjoint of level n + 1 (read); lfA/lgA/lTA: of level n
-//   (written); lf planes [N][9][n] with plane 0 the rest population;
+//   (written); lf planes [N][9][n] with plane 0 the rest population, without
+//   the part that reaches every population that formed phi C_i: that is
+//   l [N][n], at the node of phi C_i, read for level n + 1 and then written
+//   for level n;
 //   lh [2N + 4][n] the history adjoint, updated in place;
 //   a [adj_planes(N)][n] intermediates of one reverse step;
 //   gE [N-1][n], gpsi [n], ggpsi [2][n]: dJ/dE_i, the pointwise part of
@@ -52,6 +54,7 @@ template <class R>
 struct AdjBufs {
   const R* lfB;
   R* lfA;
+  R* l;
   const R* lgB;
   R* lgA;
   R* lh;

@@ -12,20 +12,26 @@
 // stencil applied as a divergence, and the two-point div(psi grad .) by
 // itself (it is symmetric in the node pair); pull streaming becomes a push.
 //
-// Kernels of one reverse step (one node per thread, no workgroup barriers):
-//   k_adj_frac  forward: phi C_i (pulled), their sum, C_i, phi rho
-//   k_adj_mu    forward: phi mu_i (eq. 2.14) and mu_i = phi mu_i / psi_hat
-//   k_adj_node  recomputes the node update at x and transposes it: the
-//               adjoint of the pulled flow populations (complete, pushed to
-//               x - c_p), of the pulled phase populations (direct part), of
-//               the history at x, and per-node adjoints of every stencil
-//               input (grad C_i, grad mu_i, grad phi rho, div T, grad psi)
-//   k_adj_mid   gathers the stencil adjoints, transposes mu = phi mu /
-//               psi_hat, phi rho and phi mu_i at the node; the adjoint of T
-//               is complete here
-//   k_adj_pop   gathers the adjoint of div(psi grad C_j), transposes
-//               C_i = phi C_i / sum_j phi C_j and adds the result to every
-//               phase population that formed phi C_i
+// Kernels of one reverse step:
+//   k_adj_fields  forward: phi C_i (pulled), their sum, C_i, phi rho; phi mu_i
+//                 (eq. 2.14) and mu_i = phi mu_i / psi_hat from C and psi in
+//                 LDS (a tile and its one-node halo)
+//   k_adj_node    recomputes the node update at x and transposes it: the
+//                 adjoint of the pulled flow populations (complete, pushed to
+//                 x - c_p), of the pulled phase populations (direct part), of
+//                 the history at x, and per-node adjoints of every stencil
+//                 input (grad C_i, grad mu_i, grad phi rho, div T, grad psi);
+//                 one node per thread
+//   k_adj_mid     gathers the stencil adjoints, transposes mu = phi mu /
+//                 psi_hat, phi rho and phi mu_i, then, through LDS, the
+//                 two-point div(psi grad C_j) and C_i = phi C_i / sum_j phi
+//                 C_j; the adjoint of T is complete here
+// The adjoint of phi C_i goes, the same value, to every phase population that
+// formed phi C_i. It is kept as one plane per phase (AdjBufs::l) that the next
+// reverse step adds where it reads the populations' adjoints, instead of being
+// added to 9 N planes here. One reverse step, 256^2 N = 2 (same GPU): five
+// kernels with a launch for each stage and the populations' planes read and
+// written twice 40 us, these three 30 us.
 // The adjoint state and arithmetic are float64 for every context; the
 // forward states are read in the context's storage type (float32 contexts
 // are linearised about their own float32 trajectory).
@@ -135,59 +141,122 @@ __device__ inline double gprime2(double C) {  // g''(C), g = C^2 (C - 1)^2
 // ---------------------------------------------------------------------------
 // Forward recomputation of the fields of level n
 // ---------------------------------------------------------------------------
-template <int N, class S>
-__global__ __launch_bounds__(kThreads) void k_adj_frac(Coef<double> kd,
-                                                       AdjFwd<S> fw,
-                                                       const S* psi,
-                                                       AdjWork w) {
-  const long long n = kd.n;
-  const long long x = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (x >= n) return;
-  const int gx = int(x % kd.nx), gy = int(x / kd.nx);
-  const Nb3 b = nb3(gx, gy, kd.nx, kd.ny);
-  double pc[N], tot = 0.0;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    S mv = S(0);  // moving populations summed as the step sums them
-#pragma unroll
-    for (int p = 1; p < Q; ++p) mv += phase_plane(fw.f, i, p, Q, n)[b.pull(p)];
-    pc[i] = fw.f0[(long long)i * n + x] + double(mv);
-    tot += pc[i];
+// Tiles of the kernels that work through LDS: TX x TY nodes, a thread for each
+// and one for each node of the one-node halo, so that a tile waits on memory
+// once per stage.
+constexpr int TX = 64, TY = 4, NT = TX * TY;
+constexpr int HX = TX + 2, HY = TY + 2, RING = HX * HY - NT;
+constexpr int kTileThreads = NT + (RING + 63) / 64 * 64;
+
+// What thread t works on: position (lx, ly) of the tile with its halo (own
+// nodes first), node idx of the box. on: the thread has a position; own: it is
+// a node of the tile inside the box.
+struct TileNode {
+  int lx, ly, gx, gy;
+  bool on, own;
+};
+
+__device__ inline TileNode tile_node(int nx, int ny) {
+  TileNode t;
+  const int tid = int(threadIdx.x);
+  const unsigned gx = unsigned(nx + TX - 1) / TX;  // tiles per row
+  const int x0 = int(blockIdx.x % gx) * TX, y0 = int(blockIdx.x / gx) * TY;
+  t.on = true;
+  t.own = false;
+  if (tid < NT) {
+    t.lx = tid % TX + 1;
+    t.ly = tid / TX + 1;
+    t.own = x0 + t.lx - 1 < nx && y0 + t.ly - 1 < ny;
+  } else {
+    const int r = tid - NT;
+    t.on = r < RING;
+    if (r < HX) {
+      t.ly = 0;
+      t.lx = r;
+    } else if (r < 2 * HX) {
+      t.ly = HY - 1;
+      t.lx = r - HX;
+    } else {
+      const int q = t.on ? r - 2 * HX : 0;
+      t.ly = 1 + (q >> 1);
+      t.lx = (q & 1) ? HX - 1 : 0;
+    }
   }
-  const double inv = 1.0 / (tot > kd.psi_min ? tot : kd.psi_min);
-  double rho = 0.0;
+  t.gx = wrap(x0 + t.lx - 1, nx);
+  t.gy = wrap(y0 + t.ly - 1, ny);
+  return t;
+}
+
+template <class T>
+__device__ inline P3<T> lds3(const T (&a)[HY][HX], int lx, int ly) {
+  P3<T> p;
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const double C = pc[i] * inv;
-    w.psiC[(long long)i * n + x] = pc[i];
-    w.C[(long long)i * n + x] = C;
-    rho += kd.rho[i] * C;
-  }
-  w.tot[x] = tot;
-  w.prho[x] = double(psi[x]) * rho;
+  for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+    for (int dx = -1; dx <= 1; ++dx) p.v[dy + 1][dx + 1] = a[ly + dy][lx + dx];
+  return p;
 }
 
 template <int N, class S>
-__global__ __launch_bounds__(kThreads) void k_adj_mu(Coef<double> kd,
-                                                     const S* psi_f,
-                                                     const S* wet, AdjWork w) {
+__global__ __launch_bounds__(kTileThreads) void k_adj_fields(
+    Coef<double> kd, AdjFwd<S> fw, const S* psi_f, const S* wet, AdjWork w) {
+  __shared__ double sC[N][HY][HX];
+  __shared__ double sp[HY][HX];
   const long long n = kd.n;
-  const long long x = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (x >= n) return;
-  const int gx = int(x % kd.nx), gy = int(x / kd.nx);
-  const Nb3 b = nb3(gx, gy, kd.nx, kd.ny);
-  const P3<double> ps = load3<double>(psi_f, b);
+  const TileNode t = tile_node(kd.nx, kd.ny);
+  const Nb3 b = nb3(t.gx, t.gy, kd.nx, kd.ny);
+  const unsigned x = b.at(0, 0);
+  double C[N], E[N];
+  if (t.on) {
+    S f[N][Q - 1];
+    double f0[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int p = 1; p < Q; ++p)
+        f[i][p - 1] = phase_plane(fw.f, i, p, Q, n)[b.pull(p)];
+      f0[i] = fw.f0[(long long)i * n + x];
+    }
+    const double ps = double(psi_f[x]);
+#pragma unroll
+    for (int i = 0; i < N - 1; ++i)
+      E[i] = t.own ? double(wet[(long long)i * n + x]) : 0.0;
+    double pc[N], tot = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      S mv = S(0);  // moving populations summed as the step sums them
+#pragma unroll
+      for (int p = 1; p < Q; ++p) mv += f[i][p - 1];
+      pc[i] = f0[i] + double(mv);
+      tot += pc[i];
+    }
+    const double inv = 1.0 / (tot > kd.psi_min ? tot : kd.psi_min);
+    double rho = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      C[i] = pc[i] * inv;
+      sC[i][t.ly][t.lx] = C[i];
+      rho += kd.rho[i] * C[i];
+    }
+    sp[t.ly][t.lx] = ps;
+    if (t.own) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        w.psiC[(long long)i * n + x] = pc[i];
+        w.C[(long long)i * n + x] = C[i];
+      }
+      w.tot[x] = tot;
+      w.prho[x] = ps * rho;
+    }
+  }
+  __syncthreads();
+  if (!t.own) return;
+  const P3<double> ps = lds3(sp, t.lx, t.ly);
   const double psi = ps.v[1][1];
   const double psih = psi > kd.psi_min ? psi : kd.psi_min;
-  double C[N], L[N], E[N];
+  double L[N];
 #pragma unroll
-  for (int j = 0; j < N; ++j) {
-    const P3<double> cp = load3<double>(w.C + (long long)j * n, b);
-    C[j] = cp.v[1][1];
-    L[j] = div_psi_grad3(ps, cp);
-  }
-#pragma unroll
-  for (int i = 0; i < N - 1; ++i) E[i] = double(wet[(long long)i * n + x]);
+  for (int j = 0; j < N; ++j) L[j] = div_psi_grad3(ps, lds3(sC[j], t.lx, t.ly));
   E[N - 1] = 0.0;
   double W[N];
 #pragma unroll
@@ -357,14 +426,16 @@ __global__ __launch_bounds__(kThreads) void k_adj_node(Coef<double> kd,
     R ldel[Q], lfp[Q];
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
-      const R l = ab.lfB[(long long)(i * Q + p) * n + x];
+      // this population formed phi C_i at x + c_p
+      const R l = ab.lfB[(long long)(i * Q + p) * n + x] +
+                  ab.l[(long long)i * n + b.at(D2Q9::c[p].x, D2Q9::c[p].y)];
       ldel[p] = -l;
       lfp[p] = l;  // f*_p = f_p - del_p (the rest population too)
     }
     R lem = R(0), lXi[2] = {lX[i][0], lX[i][1]}, lV[2] = {R(0), R(0)};
     collide_phase_T<D2Q9>(ldel, k.sf, k.cs2, lfp, lem, lXi, lV);
     // pulled moving populations: pushed back to x - c_p; the rest
-    // population stays at x (k_adj_pop adds the phi C_i part to both)
+    // population stays at x (the phi C_i part of both is in ab.l)
     ab.lfA[(long long)(i * Q) * n + x] = lfp[0];
 #pragma unroll
     for (int p = 1; p < Q; ++p) ab.lfA[(long long)(i * Q + p) * n + b.pull(p)] = lfp[p];
@@ -562,128 +633,131 @@ __global__ __launch_bounds__(kThreads) void k_adj_node(Coef<double> kd,
 }
 
 // ---------------------------------------------------------------------------
-// Gathers of the stencil adjoints; phi mu_i and phi rho transposed
+// Gathers of the stencil adjoints; phi mu_i, phi rho, div(psi grad C_j) and
+// C_i = phi C_i / sum_j phi C_j transposed
 // ---------------------------------------------------------------------------
 template <int N, class S, class R>
-__global__ __launch_bounds__(kThreads) void k_adj_mid(Coef<double> kd,
-                                                      const S* psi_f,
-                                                      const S* wet, AdjWork w,
-                                                      AdjBufs<R> ab) {
+__global__ __launch_bounds__(kTileThreads) void k_adj_mid(Coef<double> kd,
+                                                          const S* psi_f,
+                                                          const S* wet,
+                                                          AdjWork w,
+                                                          AdjBufs<R> ab) {
   using D = double;
+  __shared__ D sL[N][HY][HX], sC[N][HY][HX], sp[HY][HX];
   const long long n = kd.n;
-  const long long x = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (x >= n) return;
-  const int gx = int(x % kd.nx), gy = int(x / kd.nx);
-  const Nb3 b = nb3(gx, gy, kd.nx, kd.ny);
+  const TileNode t = tile_node(kd.nx, kd.ny);
+  const Nb3 b = nb3(t.gx, t.gy, kd.nx, kd.ny);
+  const unsigned x = b.at(0, 0);
   const R* a = ab.a;
   auto plane = [&](int q) { return a + (long long)q * n; };
-  const D psi = D(psi_f[x]);
-  const D psih = psi > kd.psi_min ? psi : kd.psi_min;
-  const bool psi_floor = !(psi > kd.psi_min);
-  D lpsi = 0.0;
-  // adjoint of T^{n-1}: complete
-  ab.lTA[x] = grad_T(load3<R>(plane(adj_T<N>()), b),
-                     load3<R>(plane(adj_T<N>() + 1), b));
-  // phi rho = psi sum_i rho_i C_i
-  const D lpr = D(a[(long long)adj_psirho<N>() * n + x]) +
-                D(grad_T(load3<R>(plane(adj_gprho<N>()), b),
-                         load3<R>(plane(adj_gprho<N>() + 1), b)));
-  D C[N], lC[N], lpm[N], E[N];
-  D rho = 0.0;
+  D psi = 0.0, psih = 1.0;
+  bool psi_floor = false;
+  D C[N], lmu[N], lpm[N];
+  // phi mu_i at the tile and its halo: the adjoint of div(psi grad C_j)
+  if (t.on) {
+    psi = D(psi_f[x]);
+    psih = psi > kd.psi_min ? psi : kd.psi_min;
+    psi_floor = !(psi > kd.psi_min);
+    D lL[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    C[i] = w.C[(long long)i * n + x];
-    rho += kd.rho[i] * C[i];
-    lC[i] = D(a[(long long)(adj_C<N>() + i) * n + x]) +
-            D(grad_T(load3<R>(plane(adj_gC<N>() + 2 * i), b),
-                     load3<R>(plane(adj_gC<N>() + 2 * i + 1), b))) +
-            psi * kd.rho[i] * lpr;
-    // mu_i = phi mu_i / psi_hat: the stencil part of the adjoint of mu_i
-    const D lmu = D(grad_T(load3<R>(plane(adj_gmu<N>() + 2 * i), b),
-                           load3<R>(plane(adj_gmu<N>() + 2 * i + 1), b)));
-    const D pm = w.psimu[(long long)i * n + x];
-    lpm[i] = D(a[(long long)(adj_psimu<N>() + i) * n + x]) + lmu / psih;
-    if (!psi_floor) lpsi -= lmu * pm / (psih * psih);
+    for (int i = 0; i < N; ++i) {
+      C[i] = w.C[(long long)i * n + x];
+      // mu_i = phi mu_i / psi_hat: the stencil part of the adjoint of mu_i
+      lmu[i] = D(grad_T(load3<R>(plane(adj_gmu<N>() + 2 * i), b),
+                        load3<R>(plane(adj_gmu<N>() + 2 * i + 1), b)));
+      lpm[i] = D(a[(long long)(adj_psimu<N>() + i) * n + x]) + lmu[i] / psih;
+      lL[i] = 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (j != i) lL[j] += kd.grad34[i][j] * lpm[i];
+    sp[t.ly][t.lx] = psi;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      sL[j][t.ly][t.lx] = lL[j];
+      sC[j][t.ly][t.lx] = C[j];
+    }
   }
-  lpsi += rho * lpr;
+  D lpsi = 0.0, lC[N];
+  if (t.own) {
+    // adjoint of T^{n-1}: complete
+    ab.lTA[x] = grad_T(load3<R>(plane(adj_T<N>()), b),
+                       load3<R>(plane(adj_T<N>() + 1), b));
+    // phi rho = psi sum_i rho_i C_i
+    const D lpr = D(a[(long long)adj_psirho<N>() * n + x]) +
+                  D(grad_T(load3<R>(plane(adj_gprho<N>()), b),
+                           load3<R>(plane(adj_gprho<N>() + 1), b)));
+    D E[N];
+    D rho = 0.0;
 #pragma unroll
-  for (int i = 0; i < N - 1; ++i) E[i] = D(wet[(long long)i * n + x]);
-  E[N - 1] = 0.0;
-  // phi mu_i (eq. 2.14): bulk, gradient and wetting terms
-  D lL[N], lW[N], lE[N];
+    for (int i = 0; i < N; ++i) {
+      rho += kd.rho[i] * C[i];
+      lC[i] = D(a[(long long)(adj_C<N>() + i) * n + x]) +
+              D(grad_T(load3<R>(plane(adj_gC<N>() + 2 * i), b),
+                       load3<R>(plane(adj_gC<N>() + 2 * i + 1), b))) +
+              psi * kd.rho[i] * lpr;
+      const D pm = w.psimu[(long long)i * n + x];
+      if (!psi_floor) lpsi -= lmu[i] * pm / (psih * psih);
+    }
+    lpsi += rho * lpr;
 #pragma unroll
-  for (int j = 0; j < N; ++j) lL[j] = lW[j] = lE[j] = 0.0;
+    for (int i = 0; i < N - 1; ++i) E[i] = D(wet[(long long)i * n + x]);
+    E[N - 1] = 0.0;
+    // phi mu_i (eq. 2.14): bulk and wetting terms
+    D lW[N], lE[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    D bulk = 0.0, curv = 0.0;
-    const D g2i = gprime2(C[i]);
-    const D gi = gprime(C[i]);
+    for (int j = 0; j < N; ++j) lW[j] = lE[j] = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      D bulk = 0.0, curv = 0.0;
+      const D g2i = gprime2(C[i]);
+      const D gi = gprime(C[i]);
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (j != i) {
+          bulk += kd.beta2[i][j] * (gi - gprime(C[i] + C[j]));
+          const D g2ij = gprime2(C[i] + C[j]);
+          curv += kd.beta2[i][j] * (g2i - g2ij);
+          lC[j] -= psi * lpm[i] * kd.beta2[i][j] * g2ij;
+          lW[j] += kd.wet3[i][j] * lpm[i];
+        }
+      lC[i] += psi * lpm[i] * curv;
+      lpsi += bulk * lpm[i];
+    }
+    // W_j = sum_{q != j} c_jq C_j C_q, c_jq = (s_jN E_j - s_qN E_q) / s_jq
 #pragma unroll
     for (int j = 0; j < N; ++j)
-      if (j != i) {
-        bulk += kd.beta2[i][j] * (gi - gprime(C[i] + C[j]));
-        const D g2ij = gprime2(C[i] + C[j]);
-        curv += kd.beta2[i][j] * (g2i - g2ij);
-        lC[j] -= psi * lpm[i] * kd.beta2[i][j] * g2ij;
-        lL[j] += kd.grad34[i][j] * lpm[i];
-        lW[j] += kd.wet3[i][j] * lpm[i];
-      }
-    lC[i] += psi * lpm[i] * curv;
-    lpsi += bulk * lpm[i];
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        if (q != j) {
+          const D cjq = (kd.sigN[j] * E[j] - kd.sigN[q] * E[q]) * kd.inv_sig[j][q];
+          lC[j] += lW[j] * cjq * C[q];
+          lC[q] += lW[j] * cjq * C[j];
+          const D lc = lW[j] * C[j] * C[q];
+          lE[j] += kd.sigN[j] * kd.inv_sig[j][q] * lc;
+          lE[q] -= kd.sigN[q] * kd.inv_sig[j][q] * lc;
+        }
+#pragma unroll
+    for (int i = 0; i < N - 1; ++i) ab.gE[(long long)i * n + x] += lE[i];
   }
-  // W_j = sum_{q != j} c_jq C_j C_q, c_jq = (s_jN E_j - s_qN E_q) / s_jq
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int q = 0; q < N; ++q)
-      if (q != j) {
-        const D cjq = (kd.sigN[j] * E[j] - kd.sigN[q] * E[q]) * kd.inv_sig[j][q];
-        lC[j] += lW[j] * cjq * C[q];
-        lC[q] += lW[j] * cjq * C[j];
-        const D lc = lW[j] * C[j] * C[q];
-        lE[j] += kd.sigN[j] * kd.inv_sig[j][q] * lc;
-        lE[q] -= kd.sigN[q] * kd.inv_sig[j][q] * lc;
-      }
-  R* aw = ab.a;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    aw[(long long)(adj_C<N>() + i) * n + x] = R(lC[i]);
-    aw[(long long)(adj_L<N>() + i) * n + x] = R(lL[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < N - 1; ++i) ab.gE[(long long)i * n + x] += lE[i];
-  ab.gpsi[x] += lpsi;
-}
-
-// ---------------------------------------------------------------------------
-// div(psi grad C_j) and C_i = phi C_i / sum_j phi C_j transposed; the phase
-// population adjoint
-// ---------------------------------------------------------------------------
-template <int N, class S, class R>
-__global__ __launch_bounds__(kThreads) void k_adj_pop(Coef<double> kd,
-                                                      const S* psi_f, AdjWork w,
-                                                      AdjBufs<R> ab) {
-  using D = double;
-  const long long n = kd.n;
-  const long long x = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (x >= n) return;
-  const int gx = int(x % kd.nx), gy = int(x / kd.nx);
-  const Nb3 b = nb3(gx, gy, kd.nx, kd.ny);
-  const P3<D> ps = load3<D>(psi_f, b);
-  D lC[N], C[N], lpsi = 0.0;
+  __syncthreads();
+  if (!t.own) return;
+  const P3<D> ps = lds3(sp, t.lx, t.ly);
+  D lpop = 0.0;
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    const P3<D> al = load3<D>(ab.a + (long long)(adj_L<N>() + j) * n, b);
-    const P3<D> cp = load3<D>(w.C + (long long)j * n, b);
-    C[j] = cp.v[1][1];
+    const P3<D> al = lds3(sL[j], t.lx, t.ly);
+    const P3<D> cp = lds3(sC[j], t.lx, t.ly);
     // the two-point operator is symmetric: its transpose is itself
-    lC[j] = D(ab.a[(long long)(adj_C<N>() + j) * n + x]) + div_psi_grad3(ps, al);
+    lC[j] += div_psi_grad3(ps, al);
 #pragma unroll
     for (int dy = -1; dy <= 1; ++dy)
 #pragma unroll
       for (int dx = -1; dx <= 1; ++dx)
         if (dx || dy)
-          lpsi += wdiv(dx, dy) * (al.v[1][1] - al.v[dy + 1][dx + 1]) *
+          lpop += wdiv(dx, dy) * (al.v[1][1] - al.v[dy + 1][dx + 1]) *
                   (cp.v[dy + 1][dx + 1] - cp.v[1][1]);
   }
   const D tot = w.tot[x];
@@ -698,15 +772,12 @@ __global__ __launch_bounds__(kThreads) void k_adj_pop(Coef<double> kd,
 #pragma unroll
     for (int i = 0; i < N; ++i) lpc[i] = lC[i] / kd.psi_min;
   }
+  // phi C_i = f^i_0(x) + sum_{p >= 1} f^i_p(x - c_p)
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const R l = R(D(ab.a[(long long)(adj_psiC<N>() + i) * n + x]) + lpc[i]);
-    // phi C_i = f^i_0(x) + sum_{p >= 1} f^i_p(x - c_p)
-    ab.lfA[(long long)(i * Q) * n + x] += l;
-#pragma unroll
-    for (int p = 1; p < Q; ++p) ab.lfA[(long long)(i * Q + p) * n + b.pull(p)] += l;
-  }
-  ab.gpsi[x] += lpsi;
+  for (int i = 0; i < N; ++i)
+    ab.l[(long long)i * n + x] =
+        R(D(a[(long long)(adj_psiC<N>() + i) * n + x]) + lpc[i]);
+  ab.gpsi[x] = (ab.gpsi[x] + lpsi) + lpop;
 }
 
 // ---------------------------------------------------------------------------
@@ -851,13 +922,13 @@ hipError_t adj_step_n(const Coef<double>& kd, const AdjFwd<S>& fw,
                       const S* psi, const S* wet, const AdjWork& w,
                       const AdjBufs<double>& ab, hipStream_t st) {
   const dim3 g(blocks_for(kd.n)), t(kThreads);
-  hipLaunchKernelGGL((k_adj_frac<N, S>), g, t, 0, st, kd, fw, psi, w);
-  hipLaunchKernelGGL((k_adj_mu<N, S>), g, t, 0, st, kd, psi, wet, w);
+  const dim3 gt(unsigned((kd.nx + TX - 1) / TX) * unsigned((kd.ny + TY - 1) / TY));
+  const dim3 tt(kTileThreads);
+  hipLaunchKernelGGL((k_adj_fields<N, S>), gt, tt, 0, st, kd, fw, psi, wet, w);
   hipLaunchKernelGGL((k_adj_node<N, S, double>), g, t, 0, st, kd, kd, fw, psi,
                      w, ab);
-  hipLaunchKernelGGL((k_adj_mid<N, S, double>), g, t, 0, st, kd, psi, wet, w,
+  hipLaunchKernelGGL((k_adj_mid<N, S, double>), gt, tt, 0, st, kd, psi, wet, w,
                      ab);
-  hipLaunchKernelGGL((k_adj_pop<N, S, double>), g, t, 0, st, kd, psi, w, ab);
   return hipGetLastError();
 }
 

@@ -215,13 +215,15 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
 
   const size_t sfl = (size_t)N * 9 * n, sgl = 9 * n, shl = (size_t)c->nhist * n;
   const size_t sal = (size_t)adj_planes(N) * n;
-  const size_t adj_count = 2 * sfl + 2 * sgl + shl + 2 * n + sal;
+  const size_t sl = (size_t)N * n;
+  const size_t adj_count = 2 * sfl + 2 * sgl + shl + 2 * n + sal + sl;
   ACHK(adj.alloc(adj_count * sizeof(R)), "hipMalloc adjoint");
   R* lf[2] = {adj.as<R>(), adj.as<R>() + sfl};
   R* lg[2] = {lf[1] + sfl, lf[1] + sfl + sgl};
   R* lh = lg[1] + sgl;
   R* lT[2] = {lh + shl, lh + shl + n};
   R* a = lT[1] + n;
+  R* l = a + sal;
 
   ACHK(work.alloc((size_t)(4 * N + 2) * n * sizeof(double)), "hipMalloc work");
   AdjWork w;
@@ -313,6 +315,7 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
       AdjBufs<R> ab;
       ab.lfB = lf[la];
       ab.lfA = lf[la ^ 1];
+      ab.l = l;
       ab.lgB = lg[la];
       ab.lgA = lg[la ^ 1];
       ab.lh = lh;
