@@ -1,7 +1,8 @@
 // Host side of ddcc_adjoint (include/ddcc.h): forward sweep with periodic
 // checkpoints, objective and seed, reverse sweep segment by segment
 // (recomputing each segment's states from its checkpoint, the step kernel
-// writing each state straight into its slot), final gradients. The states
+// writing each state straight into its slot; the last segment's are kept by
+// the forward sweep), final gradients. The states
 // of the next segment are recomputed on a second stream while the reverse
 // sweep runs over the current one, into the other of two segment buffers.
 #include <hip/hip_runtime.h>
@@ -34,22 +35,27 @@ struct DevMem {
   }
 };
 
-// A second stream (default priority) and the events that order the two
-// segment buffers between it and the context stream; released on return.
+// The context's second stream (default priority) and the events that order
+// the two segment buffers between it and the context stream; the stream is
+// drained on return.
 struct Pipe {
   hipStream_t aux = nullptr;
-  hipEvent_t ready[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr};
+  hipEvent_t *ready = nullptr, *freed = nullptr;  // [2] each
   hipEvent_t start = nullptr;
   ~Pipe() {
     if (aux) (void)hipStreamSynchronize(aux);
-    for (hipEvent_t e : {ready[0], ready[1], freed[0], freed[1], start})
-      if (e) (void)hipEventDestroy(e);
-    if (aux) (void)hipStreamDestroy(aux);
   }
-  hipError_t init() {
-    hipError_t e = hipStreamCreateWithFlags(&aux, hipStreamNonBlocking);
-    for (hipEvent_t* ev : {&ready[0], &ready[1], &freed[0], &freed[1], &start})
-      if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+  hipError_t init(ddcc_ctx* c) {
+    hipError_t e = hipSuccess;
+    if (!c->adj_stream)
+      e = hipStreamCreateWithFlags(&c->adj_stream, hipStreamNonBlocking);
+    for (hipEvent_t& ev : c->adj_events)
+      if (e == hipSuccess && !ev)
+        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    aux = c->adj_stream;
+    ready = c->adj_events;
+    freed = c->adj_events + 2;
+    start = c->adj_events[4];
     return e;
   }
 };
@@ -78,8 +84,9 @@ Layout state_layout(const ddcc_ctx* c) {
   return L;
 }
 
-// Copy the context's current state (populations, history, T) into a slot.
-hipError_t save_state(ddcc_ctx* c, char* slot, const Layout& L) {
+// Copy the context's current state (populations, history, T) into a slot, or
+// a slot into the context's current level.
+hipError_t copy_state(ddcc_ctx* c, char* slot, const Layout& L, bool to_slot) {
   const size_t n = (size_t)c->n;
   struct Part {
     void* dev;
@@ -92,7 +99,8 @@ hipError_t save_state(ddcc_ctx* c, char* slot, const Layout& L) {
       {c->T[c->cur], L.sf + L.s0 + L.sg + L.sh, (size_t)c->nT * n * c->esz}};
   for (const Part& q : parts) {
     if (!q.bytes) continue;
-    hipError_t e = hipMemcpyAsync(slot + q.off, q.dev, q.bytes,
+    hipError_t e = hipMemcpyAsync(to_slot ? slot + q.off : q.dev,
+                                  to_slot ? q.dev : slot + q.off, q.bytes,
                                   hipMemcpyDeviceToDevice, c->stream);
     if (e != hipSuccess) return e;
   }
@@ -121,16 +129,11 @@ const Coef<float>& coef_of<float>(const ddcc_ctx* c) {
   return c->kf;
 }
 
-// One forward step from the state stored in slot `from` into slot `to`
-// (the history is updated in place, so it is copied over first).
+// One forward step from the state stored in slot `from` into slot `to`.
 template <class S>
 hipError_t step_between(ddcc_ctx* c, const char* from, char* to,
                         const Layout& L, hipStream_t st) {
   const size_t oh = L.sf + L.s0 + L.sg;
-  const size_t sh = (size_t)c->nhist * (size_t)c->n * c->esz;
-  hipError_t e = hipMemcpyAsync(to + oh, from + oh, sh, hipMemcpyDeviceToDevice,
-                                st);
-  if (e != hipSuccess) return e;
   Bufs<S, S> b{};
   const AdjFwd<S> a = view<S>(from, L);
   b.fA = a.f;
@@ -140,6 +143,7 @@ hipError_t step_between(ddcc_ctx* c, const char* from, char* to,
   b.fB = reinterpret_cast<S*>(to);
   b.f0B = reinterpret_cast<double*>(to + L.sf);
   b.gB = reinterpret_cast<S*>(to + L.sf + L.s0);
+  b.histA = a.hist;
   b.hist = reinterpret_cast<S*>(to + oh);
   b.TB = reinterpret_cast<S*>(to + oh + L.sh);
   b.psi = static_cast<const S*>(c->psi);
@@ -147,8 +151,9 @@ hipError_t step_between(ddcc_ctx* c, const char* from, char* to,
   b.coef_d = c->dkd;
   b.coef_r = sizeof(S) == 8 ? static_cast<const void*>(c->dkd)
                             : static_cast<const void*>(c->dkf);
-  return launch_2d<S, S, S>(c->p.nphase, MODE_STEP, c->kd, coef_of<S>(c), b,
-                            c->tile_y, c->cus, st);
+  return launch_2d<S, S, S>(c->p.nphase,
+                            c->stream_stores ? MODE_STREAM : MODE_STEP, c->kd,
+                            coef_of<S>(c), b, c->tile_y, c->cus, st);
 }
 
 int forward_step(ddcc_ctx* c) {
@@ -252,15 +257,25 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
                       c->stream),
        "copy weights");
 
-  // forward sweep: checkpoint every `interval` steps, keep the final state
+  // forward sweep: checkpoint every `interval` steps; the last segment, the
+  // first that the reverse sweep needs, straight into its buffer
   int rc = DDCC_OK;
-  for (int64_t s = 0; s < nsteps; ++s) {
+  const int64_t last = nck > 0 ? (nck - 1) * interval : 0;
+  for (int64_t s = 0; s < last; ++s) {
     if (s % interval == 0)
-      ACHK(save_state(c, slot((size_t)(s / interval)), L), "checkpoint");
+      ACHK(copy_state(c, slot((size_t)(s / interval)), L, true), "checkpoint");
     rc = forward_step(c);
     if (rc) return rc;
   }
-  ACHK(save_state(c, fin, L), "checkpoint");
+  ACHK(copy_state(c, nsteps > 0 ? segbuf[0] : fin, L, true), "checkpoint");
+  for (int64_t s = last; s < nsteps; ++s) {
+    char* from = segbuf[0] + (size_t)(s - last) * L.total;
+    ACHK(step_between<S>(c, from, s + 1 < nsteps ? from + L.total : fin, L,
+                         c->stream),
+         "step kernel");
+    ++c->t;
+  }
+  if (nsteps > 0) ACHK(copy_state(c, fin, L, false), "final state");
 
   // objective on the final state
   double sw, sm;
@@ -279,7 +294,7 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
   // steps over them, the second stream recomputes segment sg - 1 into the
   // other buffer, once the reverse sweep of segment sg + 1 has released it.
   Pipe pp;
-  ACHK(pp.init(), "adjoint streams");
+  ACHK(pp.init(c), "adjoint streams");
   auto recompute = [&](int64_t sg, char* dst) -> hipError_t {
     const int64_t s0 = sg * interval;
     const int64_t s1 = s0 + interval < nsteps ? s0 + interval : nsteps;
@@ -291,14 +306,10 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
     }
     return e;
   };
-  // the checkpoints were written on the context stream (no segment at all
-  // when nsteps = 0)
-  if (nck > 0) {
-    ACHK(hipEventRecord(pp.start, c->stream), "event");
-    ACHK(hipStreamWaitEvent(pp.aux, pp.start, 0), "event");
-    ACHK(recompute(nck - 1, segbuf[0]), "step kernel");
-    ACHK(hipEventRecord(pp.ready[0], pp.aux), "event");
-  }
+  // the checkpoints, and the last segment's states, were written on the
+  // context stream
+  ACHK(hipEventRecord(pp.start, c->stream), "event");
+  ACHK(hipStreamWaitEvent(pp.aux, pp.start, 0), "event");
   int la = 0;
   for (int64_t sg = nck - 1; sg >= 0; --sg) {
     const int b = (int)((nck - 1 - sg) % 2);
@@ -308,7 +319,8 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
       ACHK(recompute(sg - 1, segbuf[b ^ 1]), "step kernel");
       ACHK(hipEventRecord(pp.ready[b ^ 1], pp.aux), "event");
     }
-    ACHK(hipStreamWaitEvent(c->stream, pp.ready[b], 0), "event");
+    if (sg < nck - 1)
+      ACHK(hipStreamWaitEvent(c->stream, pp.ready[b], 0), "event");
     const int64_t s0 = sg * interval;
     const int64_t s1 = s0 + interval < nsteps ? s0 + interval : nsteps;
     for (int64_t s = s1 - 1; s >= s0; --s) {
@@ -351,8 +363,8 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
     ACHK(hipMemcpyAsync(gpsi_host, gpsi_out, n * sizeof(double),
                         hipMemcpyDeviceToHost, c->stream),
          "copy gradient");
-  // the reverse sweep works on the stored states only: the context still
-  // holds the final level of the forward sweep
+  // the reverse sweep works on the stored states only: the context holds
+  // the final level of the forward sweep
   ACHK(hipStreamSynchronize(c->stream), "sync");
   return DDCC_OK;
 }

@@ -314,6 +314,7 @@ Bufs<Pop, S> bufs(ddcc_ctx* c, int mode) {
     b.TB = static_cast<S*>(c->T[o]);
   }
   b.hist = static_cast<S*>(c->hist);
+  b.histA = b.hist;
   b.psi = static_cast<const S*>(c->psi);
   b.wet = static_cast<const S*>(c->wet);
   if (c->work) {
@@ -384,6 +385,9 @@ void release(ddcc_ctx* c) {
                   c->dkd,   c->dkf,    c->geo64};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
+  for (hipEvent_t e : c->adj_events)
+    if (e) (void)hipEventDestroy(e);
+  if (c->adj_stream) (void)hipStreamDestroy(c->adj_stream);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
 }
 
@@ -1243,6 +1247,7 @@ Bufs<Pop, S> batch_bufs(ddcc_batch* b, int mode) {
   r.TA = static_cast<const S*>(b->T[a]);
   r.TB = static_cast<S*>(b->T[w]);
   r.hist = static_cast<S*>(b->hist);
+  r.histA = r.hist;
   r.psi = static_cast<const S*>(b->psi);
   r.wet = static_cast<const S*>(b->wet);
   return r;

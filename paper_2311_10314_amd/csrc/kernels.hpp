@@ -27,7 +27,8 @@ struct Bufs {
   double* f0B;
   const Pop* gA;
   Pop* gB;
-  S* hist;
+  S* hist;         // written; 3D: read too
+  const S* histA;  // 2D: read (hist, or the previous level's copy)
   const S* TA;
   S* TB;
   const S* psi;

@@ -578,10 +578,10 @@ struct Step2D {
       for (int p = 0; p < Q; ++p)
         in.g[p] = ldp(b.gA + (long long)p * n, nb.src(D2Q9::c[p].x, D2Q9::c[p].y));
 #pragma unroll
-      for (int q = 0; q < 2 * N; ++q) in.hX[q] = ldo<STREAM>(b.hist + (long long)q * n, idx);
+      for (int q = 0; q < 2 * N; ++q) in.hX[q] = ldo<STREAM>(b.histA + (long long)q * n, idx);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) in.hY[q] = ldo<STREAM>(b.hist + (long long)(2 * N + q) * n, idx);
-      in.hP = ldo<STREAM>(b.hist + (long long)(2 * N + 3) * n, idx);
+      for (int q = 0; q < 3; ++q) in.hY[q] = ldo<STREAM>(b.histA + (long long)(2 * N + q) * n, idx);
+      in.hP = ldo<STREAM>(b.histA + (long long)(2 * N + 3) * n, idx);
       if constexpr (F0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) in.f0[i] = ldp(b.f0A + (long long)(i) * n, idx);
@@ -673,7 +673,7 @@ struct Step2D {
       // force (eq. 3.13): -div T^{n-1} + sum_i phi mu_i grad C_i
       //                   + P^{n-1} grad psi + psi (rho a + G)
       const Patch<R> tp = patch(sm.T, mx, my);
-      const R Pprev = R(PRE3 ? in3->hP : ldo<STREAM>(b.hist + (long long)(2 * N + 3) * n, idx));
+      const R Pprev = R(PRE3 ? in3->hP : ldo<STREAM>(b.histA + (long long)(2 * N + 3) * n, idx));
       R Fp[2];
       Fp[0] = grad_y(tp) + Pprev * gpsi[0] + psirho * k.accel[0] +
               psi * k.force[0];
@@ -702,7 +702,7 @@ struct Step2D {
     if constexpr (MODE != MODE_INIT) {
 #pragma unroll
       for (int q = 0; q < 3; ++q)
-        dtY[q] = Y[q] - R(PRE3 ? in3->hY[q] : ldo<STREAM>(b.hist + (long long)(2 * N + q) * n, idx));
+        dtY[q] = Y[q] - R(PRE3 ? in3->hY[q] : ldo<STREAM>(b.histA + (long long)(2 * N + q) * n, idx));
     }
 
     // local flow rates from nu (eq. 16)
@@ -796,8 +796,8 @@ struct Step2D {
           }
         Sx *= psi;
         Sy *= psi;
-        const R dX0 = X[0] - R(PRE3 ? in3->hX[2 * i] : ldo<STREAM>(b.hist + (long long)(2 * i) * n, idx));
-        const R dX1 = X[1] - R(PRE3 ? in3->hX[2 * i + 1] : ldo<STREAM>(b.hist + (long long)(2 * i + 1) * n, idx));
+        const R dX0 = X[0] - R(PRE3 ? in3->hX[2 * i] : ldo<STREAM>(b.histA + (long long)(2 * i) * n, idx));
+        const R dX1 = X[1] - R(PRE3 ? in3->hX[2 * i + 1] : ldo<STREAM>(b.histA + (long long)(2 * i + 1) * n, idx));
         const R V[2] = {dX0 + k.cs2 * k.eta[i] * (mu[i] * gpsi[0] - Sx),
                         dX1 + k.cs2 * k.eta[i] * (mu[i] * gpsi[1] - Sy)};
         R fp[Q];
