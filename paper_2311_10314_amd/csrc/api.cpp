@@ -377,7 +377,119 @@ bool all_finite(const double* a, size_t count) {
   return true;
 }
 
+// Steps of a small box in captured groups. A launch costs the host 2.5 to 4
+// us, and a step of a box of up to kGraphNodes nodes 6 to 10 us of one stream
+// (three launches in 3D): a program that runs a few such boxes at once waits
+// for launches. A captured group costs about 18 us and 0.25 us per step. The
+// groups are made once a context has run kGraphAfter steps one by one (making
+// them costs as much as launching their steps, and the steps already queued
+// cover it); every call starts with kGraphLead steps one by one, so that the
+// device has work while the first group is handed over. Passes over three
+// contexts in turn (same GPU): 96 x 70 FP32, 200 steps 774 -> 491 us; 128^2
+// FP64, 100 steps 381 -> 321 us. One context alone waits for its kernels
+// either way (96 x 70 FP32 6.6 -> 6.4 us per step).
+constexpr long long kGraphNodes = 1 << 17;
+constexpr int64_t kGraphAfter = 128;
+constexpr int64_t kGraphLead = 8;
+constexpr int kGraphSteps[2] = {64, 16};  // even: cur keeps its parity
+
+void drop_step_graphs(ddcc_ctx* c) {
+  for (auto& by_parity : c->step_graph)
+    for (hipGraphExec_t& g : by_parity)
+      if (g) {
+        (void)hipGraphExecDestroy(g);
+        g = nullptr;
+      }
+}
+
+// Whether steps may be launched as groups now: a small box, past its first
+// steps, on a stream that the caller is not capturing.
+bool graphs_usable(ddcc_ctx* c) {
+  if (c->n > kGraphNodes || c->graphs_failed || c->direct_steps < kGraphAfter)
+    return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(c->stream, &st) == hipSuccess &&
+         st == hipStreamCaptureStatusNone;
+}
+
+// The captured group of kGraphSteps[q] steps from the current parity, made on
+// a stream of the context's own (nothing else can be recorded there); nullptr
+// if that failed.
+hipGraphExec_t step_graph(ddcc_ctx* c, int q) {
+  if (c->graph_tile != c->tile_y) {
+    if (c->graph_tile && hipStreamSynchronize(c->stream) != hipSuccess)
+      return nullptr;
+    drop_step_graphs(c);
+    c->graph_tile = c->tile_y;
+  }
+  hipGraphExec_t& exec = c->step_graph[q][c->cur];
+  if (exec || c->graphs_failed) return exec;
+  // the calls below are allowed whatever else this thread captures
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  hipError_t e = hipSuccess;
+  if (!c->capture_stream)
+    e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
+  if (e == hipSuccess)
+    e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeRelaxed);
+  if (e == hipSuccess) {
+    const hipStream_t stream = c->stream;
+    const int cur = c->cur;
+    c->stream = c->capture_stream;
+    for (int s = 0; s < kGraphSteps[q] && e == hipSuccess; ++s) {
+      e = launch(c, MODE_STEP, nullptr, nullptr, nullptr, nullptr, nullptr,
+                 nullptr);
+      c->cur ^= 1;
+    }
+    c->stream = stream;
+    c->cur = cur;
+    hipGraph_t graph = nullptr;
+    const hipError_t end = hipStreamEndCapture(c->capture_stream, &graph);
+    if (e == hipSuccess) e = end;
+    if (e == hipSuccess)
+      e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    if (graph) (void)hipGraphDestroy(graph);
+  }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    exec = nullptr;
+    c->graphs_failed = true;
+  }
+  return exec;
+}
+
+// nsteps steps with nothing between them.
+hipError_t run_steps(ddcc_ctx* c, int64_t nsteps) {
+  const bool groups =
+      nsteps >= kGraphLead + kGraphSteps[1] && graphs_usable(c);
+  for (int64_t s = 0; s < nsteps;) {
+    if (groups && s >= kGraphLead) {
+      const int q = nsteps - s >= kGraphSteps[0] ? 0 : 1;
+      const hipGraphExec_t g =
+          nsteps - s >= kGraphSteps[q] ? step_graph(c, q) : nullptr;
+      if (g) {
+        const hipError_t e = hipGraphLaunch(g, c->stream);
+        if (e != hipSuccess) return e;
+        s += kGraphSteps[q];
+        c->t += kGraphSteps[q];
+        continue;
+      }
+    }
+    const hipError_t e = launch(c, MODE_STEP, nullptr, nullptr, nullptr,
+                                nullptr, nullptr, nullptr);
+    if (e != hipSuccess) return e;
+    c->cur ^= 1;
+    ++c->t;
+    ++c->direct_steps;
+    ++s;
+  }
+  return hipSuccess;
+}
+
 void release(ddcc_ctx* c) {
+  drop_step_graphs(c);
+  if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
   void* ptrs[] = {c->f[0],  c->f[1],   c->f0[0],    c->f0[1], c->g[0],
                   c->g[1],  c->T[0],   c->T[1],     c->hist,  c->psi,
                   c->wet,   c->staging, c->partial, c->bad,  c->work,
@@ -735,12 +847,15 @@ int ddcc_step(ddcc_ctx* c, int64_t nsteps) {
   if (!c) return DDCC_E_INVAL;
   if (nsteps < 0) return fail(c, DDCC_E_INVAL, "nsteps < 0");
   if (!c->fields_ok) return fail(c, DDCC_E_STATE, "init_fields first");
-  for (int64_t s = 0; s < nsteps; ++s) {
-    hipError_t e = launch(c, MODE_STEP, nullptr, nullptr, nullptr, nullptr,
-                          nullptr, nullptr);
+  for (int64_t left = nsteps; left > 0;) {
+    int64_t k = left;  // up to the next check
+    if (c->diag_every > 0) {
+      const int64_t gap = c->diag_every - c->t % c->diag_every;
+      if (gap < k) k = gap;
+    }
+    hipError_t e = run_steps(c, k);
     if (e != hipSuccess) return hip_fail(c, e, "step kernel");
-    c->cur ^= 1;
-    ++c->t;
+    left -= k;
     if (c->diag_every > 0 && c->t % c->diag_every == 0) {
       e = mass_into(c, c->diag_partial, nullptr, c->diag_first,
                     (long long)c->t);

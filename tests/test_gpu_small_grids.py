@@ -8,6 +8,7 @@ tile; boxes at most 32 nodes wide 32 x 8 tiles. Bars: the method's own, FP64
 1e-10 and FP32 1e-5 on C_i and u; FP16 storage (three phases: the plane
 pipeline) as in test_gpu_halfstore, C 10 u_s and u 50 u_s with u_s = 2^-11.
 """
+import numpy as np
 import pytest
 
 from paper_2311_10314_amd import workloads as W
@@ -65,3 +66,31 @@ def test_half_storage_three_phases(lattice):
     prm = {"d0": 0.3} if lattice == "D3Q7" else {}
     _check(W.random_small(3, 3, (11, 22, 70), seed=44, lattice_f=lattice,
                           **prm), "fp16", 3)
+
+
+@pytest.mark.parametrize("dim,shape,precision", [(2, (40, 70), "fp32"),
+                                                 (2, (33, 64), "fp64"),
+                                                 (3, (8, 9, 20), "fp32")])
+def test_captured_steps_equal_single_steps(dim, shape, precision):
+    """Small boxes launch long calls as captured groups of steps: several
+    calls, even and odd, with read-outs, masses and a tile change between
+    them, against a context that is stepped one by one, bit for bit."""
+    from paper_2311_10314_amd.ddcc import Sim
+    wl = W.random_small(dim, 2, shape, seed=45)
+    a = Sim.from_workload(wl, precision)
+    b = Sim.from_workload(wl, precision)
+    for k, n in enumerate([128, 150, 201, 90, 300]):
+        if k == 3:
+            a.set_tile(0, 4)
+            b.set_tile(0, 4)
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        x, y = a.read_moments(), b.read_moments()
+        print(shape, "after", a.time, flush=True)
+        assert a.time == b.time
+        assert all(np.array_equal(p, q) for p, q in zip(x, y))
+        assert np.array_equal(a.mass(), b.mass())
+        assert np.array_equal(a.save(), b.save())
+    a.close()
+    b.close()
