@@ -294,8 +294,8 @@ const char* ddcc_version(void);
 
 /* ---- Batches of independent boxes -----------------------------------------
  * Many independent 2D D2Q9 instances of the same method and parameters, on
- * grids of different sizes, advanced together: one persistent kernel launch
- * per time step drains a queue of (instance, tile) work items, and
+ * grids of different sizes, advanced together: one kernel launch per time
+ * step over all (instance, tile) work items, and
  * ddcc_batch_set_graph captures groups of steps in a HIP graph. Each
  * instance's state, inputs and outputs are exactly those of a single context
  * of its size (same layouts as the single-context calls, per instance).
@@ -345,7 +345,8 @@ int ddcc_batch_read_moments(ddcc_batch* b, int i, double* C, double* u,
 /* Per-phase totals of instance i, float64 (as ddcc_mass). Synchronises. */
 int ddcc_batch_mass(ddcc_batch* b, int i, double* mass);
 
-/* Tile height of the step kernel: 4, 8 (default) or 16 rows of 64 nodes. */
+/* Tile height of the step kernel: 4 (default for DDCC_FP64), 8 (default
+ * otherwise) or 16 rows of 64 nodes. */
 int ddcc_batch_set_tile(ddcc_batch* b, int ty);
 
 /* Times `steps` steps with each tile height and keeps the fastest; the

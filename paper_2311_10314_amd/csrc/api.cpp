@@ -1261,14 +1261,11 @@ struct ddcc_batch {
   BatchInst* insts = nullptr;
   std::vector<unsigned> t0, t1;  // tile range of each instance
   unsigned ntiles = 0;
-  unsigned* counters = nullptr;  // one per step of a captured graph
   int ty = 8;
-  int blocks = 1;                // persistent workgroups per launch
   int graph_steps = 0;           // 0: one launch per step, no graph
   bool stream_stores = false;    // steps as MODE_STREAM (see ddcc_ctx)
   hipGraphExec_t gexec[2] = {nullptr, nullptr};  // by parity of cur
   int cur = 0;
-  int cus = 0;
   std::vector<char> geom_ok, fields_ok;
   int64_t t = 0;
   std::string err;
@@ -1316,7 +1313,7 @@ void batch_release(ddcc_batch* b) {
   void* ptrs[] = {b->f[0],   b->f[1], b->f0[0],    b->f0[1],    b->g[0],
                   b->g[1],   b->T[0], b->T[1],     b->hist,     b->psi,
                   b->wet,    b->staging, b->partial, b->bad, b->tiles,
-                  b->insts,  b->counters, b->kds, b->kfs};
+                  b->insts,  b->kds, b->kfs};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
@@ -1342,22 +1339,6 @@ int build_tiles(ddcc_batch* b, int ty) {
   BHIP(b, hipStreamSynchronize(b->stream), "sync");
   b->ntiles = (unsigned)tl.size();
   b->ty = ty;
-  // persistent launch: as many workgroups as stay resident at once
-  int per_cu = 0;
-  switch (b->p.precision) {
-    case DDCC_FP64:
-      per_cu = batch_blocks_per_cu<double, double, double>(b->p.nphase, ty);
-      break;
-    case DDCC_FP16:
-      per_cu = batch_blocks_per_cu<_Float16, float, float>(b->p.nphase, ty);
-      break;
-    case DDCC_BF16:
-      per_cu = batch_blocks_per_cu<__bf16, float, float>(b->p.nphase, ty);
-      break;
-    default:
-      per_cu = batch_blocks_per_cu<float, float, float>(b->p.nphase, ty);
-  }
-  b->blocks = (per_cu < 1 ? 1 : per_cu) * (b->cus < 1 ? 1 : b->cus);
   drop_graphs(b);
   return DDCC_OK;
 }
@@ -1384,10 +1365,9 @@ Bufs<Pop, S> batch_bufs(ddcc_batch* b, int mode) {
 
 template <class Pop, class S, class R>
 hipError_t batch_launch_as(ddcc_batch* b, const Coef<R>* k, int mode,
-                           unsigned t0, unsigned nt, unsigned* counter,
-                           const double* inC, const double* inU,
-                           const double* inP, double* oC, double* oU,
-                           double* oP) {
+                           unsigned t0, unsigned nt, const double* inC,
+                           const double* inU, const double* inP, double* oC,
+                           double* oU, double* oP) {
   Bufs<Pop, S> r = batch_bufs<Pop, S>(b, mode);
   if (mode == MODE_STEP && b->stream_stores) mode = MODE_STREAM;
   r.inC = inC;
@@ -1396,35 +1376,30 @@ hipError_t batch_launch_as(ddcc_batch* b, const Coef<R>* k, int mode,
   r.outC = oC;
   r.outU = oU;
   r.outP = oP;
-  long long nb = b->blocks;
-  if (nb > nt) nb = nt;
-  if (nb < 1) nb = 1;
   return launch_2d_batch<Pop, S, R>(b->p.nphase, mode, b->kds, k, r,
-                                    b->tiles + t0, b->insts, nt, counter,
-                                    (int)nb, b->ty, b->stream);
+                                    b->tiles + t0, b->insts, nt, b->ty,
+                                    b->stream);
 }
 
-// Zero *counter, then run `mode` over tiles [t0, t0 + nt).
+// Run `mode` over tiles [t0, t0 + nt).
 hipError_t batch_launch(ddcc_batch* b, int mode, unsigned t0, unsigned nt,
-                        unsigned* counter, const double* inC = nullptr,
+                        const double* inC = nullptr,
                         const double* inU = nullptr, const double* inP = nullptr,
                         double* oC = nullptr, double* oU = nullptr,
                         double* oP = nullptr) {
-  hipError_t e = launch_fill_u32(counter, 0u, 1, b->stream);
-  if (e != hipSuccess) return e;
   switch (b->p.precision) {
     case DDCC_FP64:
-      return batch_launch_as<double, double>(b, b->kds, mode, t0, nt, counter,
-                                             inC, inU, inP, oC, oU, oP);
+      return batch_launch_as<double, double>(b, b->kds, mode, t0, nt, inC, inU,
+                                             inP, oC, oU, oP);
     case DDCC_FP16:
-      return batch_launch_as<_Float16, float>(b, b->kfs, mode, t0, nt, counter,
-                                              inC, inU, inP, oC, oU, oP);
+      return batch_launch_as<_Float16, float>(b, b->kfs, mode, t0, nt, inC, inU,
+                                              inP, oC, oU, oP);
     case DDCC_BF16:
-      return batch_launch_as<__bf16, float>(b, b->kfs, mode, t0, nt, counter,
-                                            inC, inU, inP, oC, oU, oP);
+      return batch_launch_as<__bf16, float>(b, b->kfs, mode, t0, nt, inC, inU,
+                                            inP, oC, oU, oP);
     default:
-      return batch_launch_as<float, float>(b, b->kfs, mode, t0, nt, counter,
-                                           inC, inU, inP, oC, oU, oP);
+      return batch_launch_as<float, float>(b, b->kfs, mode, t0, nt, inC, inU,
+                                           inP, oC, oU, oP);
   }
 }
 
@@ -1450,9 +1425,9 @@ int batch_check(ddcc_batch* b, int i) {
   return DDCC_OK;
 }
 
-// One step of every instance; graph replays use counters [0, graph_steps).
+// One step of every instance.
 int batch_step_direct(ddcc_batch* b) {
-  hipError_t e = batch_launch(b, MODE_STEP, 0, b->ntiles, b->counters);
+  hipError_t e = batch_launch(b, MODE_STEP, 0, b->ntiles);
   if (e != hipSuccess) return bhip(b, e, "batch step kernel");
   b->cur ^= 1;
   ++b->t;
@@ -1464,29 +1439,9 @@ int batch_capture(ddcc_batch* b) {
   hipGraph_t graph = nullptr;
   BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal),
        "begin capture");
-  hipError_t e = launch_fill_u32(b->counters, 0u, b->graph_steps, b->stream);
+  hipError_t e = hipSuccess;
   for (int s = 0; s < b->graph_steps && e == hipSuccess; ++s) {
-    switch (b->p.precision) {
-      case DDCC_FP64:
-        e = batch_launch_as<double, double>(b, b->kds, MODE_STEP, 0, b->ntiles,
-                                            b->counters + s, nullptr, nullptr,
-                                            nullptr, nullptr, nullptr, nullptr);
-        break;
-      case DDCC_FP16:
-        e = batch_launch_as<_Float16, float>(b, b->kfs, MODE_STEP, 0, b->ntiles,
-                                             b->counters + s, nullptr, nullptr,
-                                             nullptr, nullptr, nullptr, nullptr);
-        break;
-      case DDCC_BF16:
-        e = batch_launch_as<__bf16, float>(b, b->kfs, MODE_STEP, 0, b->ntiles,
-                                           b->counters + s, nullptr, nullptr,
-                                           nullptr, nullptr, nullptr, nullptr);
-        break;
-      default:
-        e = batch_launch_as<float, float>(b, b->kfs, MODE_STEP, 0, b->ntiles,
-                                          b->counters + s, nullptr, nullptr,
-                                          nullptr, nullptr, nullptr, nullptr);
-    }
+    e = batch_launch(b, MODE_STEP, 0, b->ntiles);
     b->cur ^= 1;
   }
   b->cur = par;
@@ -1543,9 +1498,7 @@ int ddcc_batch_create(const ddcc_params* p, int count, const int* nx,
   b->esz = q.precision == DDCC_FP64 ? 8 : 4;
   b->pesz = q.precision == DDCC_FP64 ? 8 : (q.precision == DDCC_FP32 ? 4 : 2);
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount,
-                            dev) != hipSuccess) {
+  if (hipGetDevice(&dev) != hipSuccess) {
     delete b;
     return DDCC_E_HIP;
   }
@@ -1586,7 +1539,6 @@ int ddcc_batch_create(const ddcc_params* p, int count, const int* nx,
   if (e == hipSuccess)
     e = hipMalloc(&b->partial, (size_t)b->mass_blocks * N * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&b->bad, (size_t)b->mass_blocks * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&b->counters, kMaxGraphSteps * sizeof(unsigned));
   if (e == hipSuccess) {
     std::vector<BatchInst> ins(count);
     for (int i = 0; i < count; ++i) ins[i] = BatchInst{nx[i], ny[i], b->n[i], b->off[i]};
@@ -1607,7 +1559,11 @@ int ddcc_batch_create(const ddcc_params* p, int count, const int* nx,
       e = hipMemcpy(b->kfs, vf.data(), count * sizeof(Coef<float>),
                     hipMemcpyHostToDevice);
   }
-  if (e != hipSuccess || build_tiles(b, 8) != DDCC_OK) {
+  // 64 x 4 tiles for float64 as in single boxes (128 instances of 64^2 to 256^2:
+  // 335 against 349 us per step with 64 x 8; 12 of 90 to 120 nodes a side 19.6
+  // against 24.0), 64 x 8 for float
+  if (e != hipSuccess ||
+      build_tiles(b, q.precision == DDCC_FP64 ? 4 : 8) != DDCC_OK) {
     batch_release(b);
     delete b;
     return e == hipErrorOutOfMemory ? DDCC_E_NOMEM : DDCC_E_HIP;
@@ -1709,8 +1665,7 @@ int ddcc_batch_init_fields(ddcc_batch* b, int i, const double* C,
   if (rc) return rc;
   // initialisation writes the populations of the current level in place
   hipError_t e = batch_launch(b, MODE_INIT, b->t0[i], b->t1[i] - b->t0[i],
-                              b->counters, sC, u ? sU : nullptr,
-                              P ? sP : nullptr);
+                              sC, u ? sU : nullptr, P ? sP : nullptr);
   if (e != hipSuccess) return bhip(b, e, "batch init kernel");
   BHIP(b, hipStreamSynchronize(b->stream), "sync");
   b->fields_ok[i] = 1;
@@ -1753,8 +1708,7 @@ int ddcc_batch_read_moments(ddcc_batch* b, int i, double* C, double* u,
   double* sU = sC + (size_t)N * b->ntot;
   double* sP = sU + 2 * (size_t)b->ntot;
   hipError_t e = batch_launch(b, MODE_MOMENTS, b->t0[i], b->t1[i] - b->t0[i],
-                              b->counters, nullptr, nullptr, nullptr, sC, sU,
-                              sP);
+                              nullptr, nullptr, nullptr, sC, sU, sP);
   if (e != hipSuccess) return bhip(b, e, "batch moments kernel");
   if (C) rc = copy_planes(b, i, sC, C, N, sizeof(double), hipMemcpyDeviceToHost);
   if (!rc && u) rc = copy_planes(b, i, sU, u, 2, sizeof(double), hipMemcpyDeviceToHost);

@@ -79,7 +79,7 @@ hipError_t launch_3d(int nphase, int lattice_f, int mode,
                      const Bufs<Pop, S>& b, int tx, int ty, int cus,
                      hipStream_t st);
 
-// Batches of independent 2D boxes: one work-queue entry per tile, and the
+// Batches of independent 2D boxes: one list entry per tile, and the
 // size and node offset of every instance. Each plane of each buffer holds
 // every instance, instance i at nodes [off_i, off_i + n_i); the plane stride
 // is the total node count (the n of the Coef handed to the batch kernel).
@@ -91,21 +91,14 @@ struct BatchInst {
   long long n, off;
 };
 
-// One step (or initialisation, or moment read-out) of the instances whose
-// tiles are listed: a persistent launch of nblocks workgroups that drain the
-// tile queue; *counter must be zero at launch. kd, k: device tables of the
-// coefficients of every instance.
+// One step (or initialisation, or moment read-out) of the ntiles >= 1 tiles
+// listed, one workgroup each. kd, k: device tables of the coefficients of
+// every instance.
 template <class Pop, class S, class R>
 hipError_t launch_2d_batch(int nphase, int mode, const Coef<double>* kd,
-                           const Coef<R>* k,
-                           const Bufs<Pop, S>& b, const BatchTile* tiles,
-                           const BatchInst* insts, unsigned ntiles,
-                           unsigned* counter, int nblocks, int ty,
-                           hipStream_t st);
-
-// Resident workgroups per compute unit of the batch kernel (0 on error).
-template <class Pop, class S, class R>
-int batch_blocks_per_cu(int nphase, int ty);
+                           const Coef<R>* k, const Bufs<Pop, S>& b,
+                           const BatchTile* tiles, const BatchInst* insts,
+                           unsigned ntiles, int ty, hipStream_t st);
 
 // Geometry from K walls: psi = prod_k psi_k and the wetting weights
 // E_i = sum_k cos theta^k_iN |grad psi_k| (i < N-1), the gradient by the
@@ -118,10 +111,6 @@ hipError_t launch_wet_field(const double* psik, const double* ctk, int K,
                             int nm1, int nx, int ny, int nz, S* psi_out,
                             S* wet_out, long long plane_stride, long long off,
                             hipStream_t st);
-
-// dst[i] = v for i < count (a kernel, so that it can sit in a captured graph).
-hipError_t launch_fill_u32(unsigned* dst, unsigned v, long long count,
-                           hipStream_t st);
 
 // Per-phase sums of all populations (rest plane f0 [N][stride_n] plus
 // the moving planes of f [N][Q-1][stride_n], nodes [0, n) of each plane) into

@@ -97,11 +97,6 @@ __global__ void k_convert(const double* src, S* dst, long long count) {
     dst[i] = S(src[i]);
 }
 
-__global__ void k_fill_u32(unsigned* dst, unsigned v, long long count) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) dst[i] = v;
-}
-
 // Wetting weights of K walls (see launch_wet_field). One node per thread.
 template <class S>
 __global__ void k_wet_field(const double* psik, const double* ctk, int K,
@@ -245,14 +240,6 @@ template hipError_t launch_wet_field<double>(const double*, const double*, int,
 template hipError_t launch_wet_field<float>(const double*, const double*, int,
                                             int, int, int, int, float*, float*,
                                             long long, long long, hipStream_t);
-
-hipError_t launch_fill_u32(unsigned* dst, unsigned v, long long count,
-                           hipStream_t st) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((count + 255) / 256)),
-                     dim3(256), 0, st, dst, v, count);
-  return hipGetLastError();
-}
 
 template <class S>
 hipError_t launch_mass(const double* f0, const S* f, int nphase, int Q,
