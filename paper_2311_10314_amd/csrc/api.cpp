@@ -339,6 +339,7 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
   b.outC = oC;
   b.outU = oU;
   b.outP = oP;
+  b.out_n = c->n;
   if (c->p.dim == 2)
     return launch_2d<Pop, S, R>(c->p.nphase, mode, c->kd, k, b, c->tile_y,
                                 c->cus, c->stream);
@@ -1367,7 +1368,7 @@ template <class Pop, class S, class R>
 hipError_t batch_launch_as(ddcc_batch* b, const Coef<R>* k, int mode,
                            unsigned t0, unsigned nt, const double* inC,
                            const double* inU, const double* inP, double* oC,
-                           double* oU, double* oP) {
+                           double* oU, double* oP, long long out_n) {
   Bufs<Pop, S> r = batch_bufs<Pop, S>(b, mode);
   if (mode == MODE_STEP && b->stream_stores) mode = MODE_STREAM;
   r.inC = inC;
@@ -1376,6 +1377,7 @@ hipError_t batch_launch_as(ddcc_batch* b, const Coef<R>* k, int mode,
   r.outC = oC;
   r.outU = oU;
   r.outP = oP;
+  r.out_n = out_n;
   return launch_2d_batch<Pop, S, R>(b->p.nphase, mode, b->kds, k, r,
                                     b->tiles + t0, b->insts, nt, b->ty,
                                     b->stream);
@@ -1386,20 +1388,20 @@ hipError_t batch_launch(ddcc_batch* b, int mode, unsigned t0, unsigned nt,
                         const double* inC = nullptr,
                         const double* inU = nullptr, const double* inP = nullptr,
                         double* oC = nullptr, double* oU = nullptr,
-                        double* oP = nullptr) {
+                        double* oP = nullptr, long long out_n = 0) {
   switch (b->p.precision) {
     case DDCC_FP64:
       return batch_launch_as<double, double>(b, b->kds, mode, t0, nt, inC, inU,
-                                             inP, oC, oU, oP);
+                                             inP, oC, oU, oP, out_n);
     case DDCC_FP16:
       return batch_launch_as<_Float16, float>(b, b->kfs, mode, t0, nt, inC, inU,
-                                              inP, oC, oU, oP);
+                                              inP, oC, oU, oP, out_n);
     case DDCC_BF16:
       return batch_launch_as<__bf16, float>(b, b->kfs, mode, t0, nt, inC, inU,
-                                            inP, oC, oU, oP);
+                                            inP, oC, oU, oP, out_n);
     default:
       return batch_launch_as<float, float>(b, b->kfs, mode, t0, nt, inC, inU,
-                                           inP, oC, oU, oP);
+                                           inP, oC, oU, oP, out_n);
   }
 }
 
@@ -1704,16 +1706,26 @@ int ddcc_batch_read_moments(ddcc_batch* b, int i, double* C, double* u,
   if (rc) return rc;
   if (!b->fields_ok[i]) return bfail(b, DDCC_E_STATE, "init_fields first");
   const int N = b->p.nphase;
+  // the instance's planes one after another, so that each field is one copy
+  const size_t n = (size_t)b->n[i];
   double* sC = b->staging;
-  double* sU = sC + (size_t)N * b->ntot;
-  double* sP = sU + 2 * (size_t)b->ntot;
+  double* sU = sC + (size_t)N * n;
+  double* sP = sU + 2 * n;
+  const long long o = b->off[i];  // the kernel's node index starts there
   hipError_t e = batch_launch(b, MODE_MOMENTS, b->t0[i], b->t1[i] - b->t0[i],
-                              nullptr, nullptr, nullptr, sC, sU, sP);
+                              nullptr, nullptr, nullptr, sC - o, sU - o, sP - o,
+                              (long long)n);
   if (e != hipSuccess) return bhip(b, e, "batch moments kernel");
-  if (C) rc = copy_planes(b, i, sC, C, N, sizeof(double), hipMemcpyDeviceToHost);
-  if (!rc && u) rc = copy_planes(b, i, sU, u, 2, sizeof(double), hipMemcpyDeviceToHost);
-  if (!rc && P) rc = copy_planes(b, i, sP, P, 1, sizeof(double), hipMemcpyDeviceToHost);
-  if (rc) return rc;
+  const struct {
+    double* host;
+    const double* dev;
+    size_t planes;
+  } parts[3] = {{C, sC, (size_t)N}, {u, sU, 2}, {P, sP, 1}};
+  for (const auto& q : parts)
+    if (q.host)
+      BHIP(b, hipMemcpyAsync(q.host, q.dev, q.planes * n * sizeof(double),
+                             hipMemcpyDeviceToHost, b->stream),
+           "copy moments");
   BHIP(b, hipStreamSynchronize(b->stream), "sync");
   return DDCC_OK;
 }

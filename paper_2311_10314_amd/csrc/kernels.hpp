@@ -38,9 +38,12 @@ struct Bufs {
   const double* inC;
   const double* inU;
   const double* inP;
+  // moments: plane i of C at outC + i * out_n, of u likewise (2D; in 3D the
+  // plane stride is n)
   double* outC;
   double* outU;
   double* outP;
+  long long out_n;
   double* fC;      // 3D work fields: C_i [N][n] and mu_i [N][n], float64
   double* fmu;
   // device copies of the context's coefficients, Coef<double> and Coef<S>

@@ -730,9 +730,9 @@ struct Step2D {
 
     if constexpr (MODE == MODE_MOMENTS) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) stp<STREAM>(b.outC + (long long)(i) * n, idx, double(C[i]));
+      for (int i = 0; i < N; ++i) stp<STREAM>(b.outC + (long long)(i) * b.out_n, idx, double(C[i]));
       stp<STREAM>(b.outU, idx, double(u[0]));
-      stp<STREAM>(b.outU + n, idx, double(u[1]));
+      stp<STREAM>(b.outU + b.out_n, idx, double(u[1]));
       stp<STREAM>(b.outP, idx, double(P));
       return;
     }
