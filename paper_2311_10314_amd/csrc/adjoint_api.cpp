@@ -151,9 +151,8 @@ hipError_t step_between(ddcc_ctx* c, const char* from, char* to,
   b.coef_d = c->dkd;
   b.coef_r = sizeof(S) == 8 ? static_cast<const void*>(c->dkd)
                             : static_cast<const void*>(c->dkf);
-  return launch_2d<S, S, S>(c->p.nphase,
-                            c->stream_stores ? MODE_STREAM : MODE_STEP, c->kd,
-                            coef_of<S>(c), b, c->tile_y, c->cus, st);
+  return launch_2d<S, S, S>(c->p.nphase, MODE_FORK, c->kd, coef_of<S>(c), b,
+                            c->tile_y, c->cus, st);
 }
 
 int forward_step(ddcc_ctx* c) {

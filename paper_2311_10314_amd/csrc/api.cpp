@@ -314,7 +314,6 @@ Bufs<Pop, S> bufs(ddcc_ctx* c, int mode) {
     b.TB = static_cast<S*>(c->T[o]);
   }
   b.hist = static_cast<S*>(c->hist);
-  b.histA = b.hist;
   b.psi = static_cast<const S*>(c->psi);
   b.wet = static_cast<const S*>(c->wet);
   if (c->work) {
@@ -1358,7 +1357,6 @@ Bufs<Pop, S> batch_bufs(ddcc_batch* b, int mode) {
   r.TA = static_cast<const S*>(b->T[a]);
   r.TB = static_cast<S*>(b->T[w]);
   r.hist = static_cast<S*>(b->hist);
-  r.histA = r.hist;
   r.psi = static_cast<const S*>(b->psi);
   r.wet = static_cast<const S*>(b->wet);
   return r;

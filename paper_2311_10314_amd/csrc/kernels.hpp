@@ -11,7 +11,15 @@ namespace ddcc {
 // writes; the host picks it for grids whose step does not fit the 256 MB
 // memory-side cache (there it is 3-6 % faster; on cache-resident grids
 // plain stores are, by up to 19 %).
-enum { MODE_STEP = 0, MODE_INIT = 1, MODE_MOMENTS = 2, MODE_STREAM = 3 };
+// MODE_FORK (2D, FP64 and FP32) is MODE_STEP with the history read from
+// Bufs::histA, for steps from one stored state to another.
+enum {
+  MODE_STEP = 0,
+  MODE_INIT = 1,
+  MODE_MOMENTS = 2,
+  MODE_STREAM = 3,
+  MODE_FORK = 4
+};
 
 // Pointers handed to the step/init/moments kernels (by value).
 //   fA/gA/TA: current level (read), fB/gB/TB: next level (written);
@@ -27,8 +35,8 @@ struct Bufs {
   double* f0B;
   const Pop* gA;
   Pop* gB;
-  S* hist;         // written; 3D: read too
-  const S* histA;  // 2D: read (hist, or the previous level's copy)
+  S* hist;
+  const S* histA;  // MODE_FORK: the history read
   const S* TA;
   S* TB;
   const S* psi;

@@ -29,6 +29,8 @@
 // double-buffered because neighbours read it.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "coef.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
@@ -319,12 +321,19 @@ struct Step2D {
   }
 
   __device__ static void run(const Coef<D>& kd, const Coef<R>& k,
-                             const Bufs<Pop, S>& b) {
+                             const Bufs<Pop, S>& b, const Grid& gd) {
     __shared__ Smem sm;
     int x0, y0;
     tile_of(x0, y0);
+    plain(sm, kd, k, b, gd, x0, y0);
+  }
+
+  // A tile whose phases load their inputs where they use them.
+  __device__ static inline void plain(Smem& sm, const Coef<D>& kd,
+                                      const Coef<R>& k, const Bufs<Pop, S>& b,
+                                      const Grid& gd, int x0, int y0) {
     if constexpr (MODE == MODE_STREAM) {
-      body(sm, kd, k, b, Grid{k.nx, k.ny, k.n, 0u}, x0, y0);
+      body(sm, kd, k, b, gd, x0, y0);
       return;
     }
     const int tid = threadIdx.x;
@@ -334,26 +343,26 @@ struct Step2D {
     // the collision (phase 3 would otherwise load them again, after the
     // whole chunk's phase-1 traffic has gone through L2). In float64 that
     // takes the kernel to 187 VGPRs and two waves per SIMD, and is still
-    // faster (same GPU, 512^2 N = 3: 48.3 -> 42.4 us; 2048^2: 825 -> 815 us).
-    constexpr bool KEEP = MODE == MODE_STEP || MODE == MODE_STREAM;
+    // faster (same GPU, 512^2 N = 3: 48.3 -> 42.4 us; 2048^2: 825 -> 815 us;
+    // 256 instances, 64 x 8 tiles: 0.829 -> 0.756 ms per step).
+    constexpr bool KEEP = MODE != MODE_INIT && MODE != MODE_MOMENTS;
     Keep fown;
-    node1<KEEP>(sm, kd, b, kd, x0, y0, tx + 2, ty + 2, psiC, &fown);
+    node1<KEEP>(sm, kd, b, gd, x0, y0, tx + 2, ty + 2, psiC, &fown);
     for (int r = tid; r < RING1; r += NT) {
       int lx, ly;
       ring1(r, lx, ly);
-      node1(sm, kd, b, kd, x0, y0, lx, ly, dummy);
+      node1(sm, kd, b, gd, x0, y0, lx, ly, dummy);
     }
     __syncthreads();
-    node2(sm, kd, b, kd, x0, y0, tx + 1, ty + 1, psimu_d);
+    node2(sm, kd, b, gd, x0, y0, tx + 1, ty + 1, psimu_d);
     for (int r = tid; r < RING2; r += NT) {
       int mx, my;
       ring2(r, mx, my);
-      node2(sm, kd, b, kd, x0, y0, mx, my, dummy);
+      node2(sm, kd, b, gd, x0, y0, mx, my, dummy);
     }
     __syncthreads();
-    if (x0 + tx < k.nx && y0 + ty < k.ny)
-      node3<KEEP>(sm, kd, k, b, Grid{k.nx, k.ny, k.n, 0u}, x0, y0, tx, ty,
-                  psiC, psimu_d, &fown);
+    if (x0 + tx < gd.nx && y0 + ty < gd.ny)
+      node3<KEEP>(sm, kd, k, b, gd, x0, y0, tx, ty, psiC, psimu_d, &fown);
   }
 
   // The tile of a streaming step (grids larger than the memory-side cache).
@@ -375,7 +384,7 @@ struct Step2D {
                                      const Grid& gd, int x0, int y0) {
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
-    constexpr bool KEEP = MODE == MODE_STEP || MODE == MODE_STREAM;
+    constexpr bool KEEP = MODE != MODE_INIT && MODE != MODE_MOMENTS;
     constexpr int PER2 = (RING2 + NT - 1) / NT;
     D psiC[N], psimu_d[N], dummy[N];
     S Eown[N], Er[PER2][N];
@@ -530,33 +539,14 @@ struct Step2D {
                               const Bufs<Pop, S>& b, const Grid& gd, int x0,
                               int y0) {
     __shared__ Smem sm;
-    if constexpr (MODE == MODE_STREAM) {
-      body(sm, kd, k, b, gd, x0, y0);
-      return;
-    }
-    const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
-    D psiC[N], psimu_d[N], dummy[N];
-    // pulled populations kept in registers as in run() (float64, 256
-    // instances, 64 x 8 tiles: 0.829 -> 0.756 ms per step, same GPU)
-    constexpr bool KEEP = MODE == MODE_STEP || MODE == MODE_STREAM;
-    Keep fown;
-    node1<KEEP>(sm, kd, b, gd, x0, y0, tx + 2, ty + 2, psiC, &fown);
-    for (int r = tid; r < RING1; r += NT) {
-      int lx, ly;
-      ring1(r, lx, ly);
-      node1(sm, kd, b, gd, x0, y0, lx, ly, dummy);
-    }
-    __syncthreads();
-    node2(sm, kd, b, gd, x0, y0, tx + 1, ty + 1, psimu_d);
-    for (int r = tid; r < RING2; r += NT) {
-      int mx, my;
-      ring2(r, mx, my);
-      node2(sm, kd, b, gd, x0, y0, mx, my, dummy);
-    }
-    __syncthreads();
-    if (x0 + tx < gd.nx && y0 + ty < gd.ny)
-      node3<KEEP>(sm, kd, k, b, gd, x0, y0, tx, ty, psiC, psimu_d, &fown);
+    plain(sm, kd, k, b, gd, x0, y0);
+  }
+
+  // The history a step reads. The further pointer is worth a mode of its own:
+  // read through it everywhere, 512^2 N = 3 FP64 takes 42.8 instead of 41.7
+  // us, 2048^2 N = 3 FP32 376 instead of 371 us.
+  __device__ static inline const S* hist_in(const Bufs<Pop, S>& b) {
+    return MODE == MODE_FORK ? b.histA : b.hist;
   }
 
   // Phase-3 inputs of the own node from global memory (flow populations,
@@ -578,10 +568,10 @@ struct Step2D {
       for (int p = 0; p < Q; ++p)
         in.g[p] = ldp(b.gA + (long long)p * n, nb.src(D2Q9::c[p].x, D2Q9::c[p].y));
 #pragma unroll
-      for (int q = 0; q < 2 * N; ++q) in.hX[q] = ldo<STREAM>(b.histA + (long long)q * n, idx);
+      for (int q = 0; q < 2 * N; ++q) in.hX[q] = ldo<STREAM>(hist_in(b) + (long long)q * n, idx);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) in.hY[q] = ldo<STREAM>(b.histA + (long long)(2 * N + q) * n, idx);
-      in.hP = ldo<STREAM>(b.histA + (long long)(2 * N + 3) * n, idx);
+      for (int q = 0; q < 3; ++q) in.hY[q] = ldo<STREAM>(hist_in(b) + (long long)(2 * N + q) * n, idx);
+      in.hP = ldo<STREAM>(hist_in(b) + (long long)(2 * N + 3) * n, idx);
       if constexpr (F0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) in.f0[i] = ldp(b.f0A + (long long)(i) * n, idx);
@@ -673,7 +663,7 @@ struct Step2D {
       // force (eq. 3.13): -div T^{n-1} + sum_i phi mu_i grad C_i
       //                   + P^{n-1} grad psi + psi (rho a + G)
       const Patch<R> tp = patch(sm.T, mx, my);
-      const R Pprev = R(PRE3 ? in3->hP : ldo<STREAM>(b.histA + (long long)(2 * N + 3) * n, idx));
+      const R Pprev = R(PRE3 ? in3->hP : ldo<STREAM>(hist_in(b) + (long long)(2 * N + 3) * n, idx));
       R Fp[2];
       Fp[0] = grad_y(tp) + Pprev * gpsi[0] + psirho * k.accel[0] +
               psi * k.force[0];
@@ -702,7 +692,7 @@ struct Step2D {
     if constexpr (MODE != MODE_INIT) {
 #pragma unroll
       for (int q = 0; q < 3; ++q)
-        dtY[q] = Y[q] - R(PRE3 ? in3->hY[q] : ldo<STREAM>(b.histA + (long long)(2 * N + q) * n, idx));
+        dtY[q] = Y[q] - R(PRE3 ? in3->hY[q] : ldo<STREAM>(hist_in(b) + (long long)(2 * N + q) * n, idx));
     }
 
     // local flow rates from nu (eq. 16)
@@ -796,8 +786,8 @@ struct Step2D {
           }
         Sx *= psi;
         Sy *= psi;
-        const R dX0 = X[0] - R(PRE3 ? in3->hX[2 * i] : ldo<STREAM>(b.histA + (long long)(2 * i) * n, idx));
-        const R dX1 = X[1] - R(PRE3 ? in3->hX[2 * i + 1] : ldo<STREAM>(b.histA + (long long)(2 * i + 1) * n, idx));
+        const R dX0 = X[0] - R(PRE3 ? in3->hX[2 * i] : ldo<STREAM>(hist_in(b) + (long long)(2 * i) * n, idx));
+        const R dX1 = X[1] - R(PRE3 ? in3->hX[2 * i + 1] : ldo<STREAM>(hist_in(b) + (long long)(2 * i + 1) * n, idx));
         const R V[2] = {dX0 + k.cs2 * k.eta[i] * (mu[i] * gpsi[0] - Sx),
                         dX1 + k.cs2 * k.eta[i] * (mu[i] * gpsi[1] - Sy)};
         R fp[Q];
@@ -842,11 +832,18 @@ bool wide_tiles(int nx, int ny, bool fp64, int ty, int cus) {
 // two structs (about 1.5 KB) overflow the scalar registers and spill into
 // VGPR lanes; read through __restrict__ pointers they are scalar loads where
 // used (512^2 N = 3, same GPU: FP32 23.3 -> 22.4 us, FP64 49.2 -> 48.3 us).
+// gd: the box as a kernel argument, one memory round trip earlier than from the
+// table (512^2 N = 3 FP32 22.7 -> 22.5 us, N = 2 17.6 -> 17.4); streaming steps
+// take it from the table (2048^2 N = 3 FP32 375 against 382 us).
 template <int N, class Pop, class S, class R, int MODE, int TY>
 __global__ __launch_bounds__(TX* TY) void k_step2d(
     const Coef<double>* __restrict__ kd, const Coef<R>* __restrict__ k,
-    Bufs<Pop, S> b) {
-  Step2D<N, Pop, S, R, MODE, TY>::run(*kd, *k, b);
+    Bufs<Pop, S> b, Grid gd) {
+  if constexpr (MODE == MODE_STREAM)
+    Step2D<N, Pop, S, R, MODE, TY>::run(*kd, *k, b,
+                                        Grid{k->nx, k->ny, k->n, 0u});
+  else
+    Step2D<N, Pop, S, R, MODE, TY>::run(*kd, *k, b, gd);
 }
 
 template <int N, class Pop, class S, class R, int MODE, int TY>
@@ -867,9 +864,9 @@ hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
   const Coef<double>* dk = static_cast<const Coef<double>*>(b.coef_d);
   const Coef<R>* dr = static_cast<const Coef<R>*>(b.coef_r);
   if (!dk || !dr) return hipErrorInvalidValue;
-  if constexpr (MODE == MODE_STEP) {
+  const Grid gd{k.nx, k.ny, k.n, 0u};
+  if constexpr (MODE == MODE_STEP || MODE == MODE_FORK) {
     if (wide_tiles(k.nx, k.ny, sizeof(R) == 8, ty, cus)) {
-      const Grid gd{k.nx, k.ny, k.n, 0u};
       const dim3 g((k.nx + TX - 1) / TX, (k.ny + ty - 1) / ty);
       if (ty == 2)
         hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 2>), g,
@@ -886,25 +883,25 @@ hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
     case 4: {
       dim3 g((k.nx + TX - 1) / TX, (k.ny + 3) / 4);
       hipLaunchKernelGGL((k_step2d<N, Pop, S, R, MODE, 4>), g, dim3(TX * 4), 0, st,
-                         dk, dr, b);
+                         dk, dr, b, gd);
       break;
     }
     case 16: {
       dim3 g((k.nx + TX - 1) / TX, (k.ny + 15) / 16);
       hipLaunchKernelGGL((k_step2d<N, Pop, S, R, MODE, 16>), g, dim3(TX * 16), 0, st,
-                         dk, dr, b);
+                         dk, dr, b, gd);
       break;
     }
     case 2: {
       dim3 g((k.nx + TX - 1) / TX, (k.ny + 1) / 2);
       hipLaunchKernelGGL((k_step2d<N, Pop, S, R, MODE, 2>), g, dim3(TX * 2), 0, st,
-                         dk, dr, b);
+                         dk, dr, b, gd);
       break;
     }
     default: {
       dim3 g((k.nx + TX - 1) / TX, (k.ny + 7) / 8);
       hipLaunchKernelGGL((k_step2d<N, Pop, S, R, MODE, 8>), g, dim3(TX * 8), 0, st,
-                         dk, dr, b);
+                         dk, dr, b, gd);
       break;
     }
   }
@@ -921,6 +918,11 @@ hipError_t launch_mode(int mode, const Coef<double>& kd, const Coef<R>& k,
       return launch_ty<N, Pop, S, R, MODE_STREAM>(kd, k, b, ty, cus, st);
     case MODE_INIT:
       return launch_ty<N, Pop, S, R, MODE_INIT>(kd, k, b, ty, cus, st);
+    case MODE_FORK:
+      if constexpr (std::is_same_v<Pop, S>)
+        return launch_ty<N, Pop, S, R, MODE_FORK>(kd, k, b, ty, cus, st);
+      else
+        return hipErrorInvalidValue;
     default:
       return launch_ty<N, Pop, S, R, MODE_MOMENTS>(kd, k, b, ty, cus, st);
   }
