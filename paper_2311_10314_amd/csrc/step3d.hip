@@ -979,7 +979,10 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
 // / 92 / 83 / 85, FP32 77 / 54 / 45 / 51; 40^3 FP16 79 / 45 / 31 / 26; 130 x 75
 // x 101 N = 3 D3Q7 FP32 272 / 247 / 242 / 259; 110 x 100 x 90 N = 3 D3Q15 FP32
 // 373 / 325 / 306 / 310; 128^3 FP32 312 / 310 / 318 / 334 (there and above
-// every round is full and ZB stays).
+// every round is full and ZB stays). A shorter column has to promise 15 %:
+// other contexts' work may fill the idle units, and then the starts are what
+// is left (45 x 109 x 87 D3Q7 FP32, 8 -> 2 planes: alone 85 -> 75 us, three
+// contexts at once 61 -> 64).
 inline int planes_per_group(int nz, int tiles, int slots, double start,
                             int least) {
   int best = ZB;
@@ -987,7 +990,7 @@ inline int planes_per_group(int nz, int tiles, int slots, double start,
   for (int zb = ZB; zb >= least; zb /= 2) {
     const long long wgs = (long long)tiles * ((nz + zb - 1) / zb);
     const double c = double((wgs + slots - 1) / slots) * (zb + start);
-    if (zb == ZB || c < cost) {
+    if (zb == ZB || c < 0.85 * cost) {
       cost = c;
       best = zb;
     }
