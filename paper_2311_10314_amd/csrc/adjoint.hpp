@@ -17,6 +17,14 @@ struct AdjFwd {
   const S* g;
   const S* hist;
   const S* T;
+  // the state stored `bytes` later
+  __host__ __device__ AdjFwd after(long long bytes) const {
+    const auto at = [bytes](auto* p) {
+      return reinterpret_cast<decltype(p)>(
+          reinterpret_cast<const char*>(p) + bytes);
+    };
+    return AdjFwd{at(f), at(f0), at(g), at(hist), at(T)};
+  }
 };
 
 // float64 fields of the level being transposed, recomputed from AdjFwd.
@@ -27,6 +35,11 @@ struct AdjWork {
   double* prho;   // [n] phi rho
   double* psimu;  // [N][n] phi mu_i
   double* mu;     // [N][n] mu_i = phi mu_i / psi_hat
+  // the fields `count` values later
+  __host__ __device__ AdjWork after(long long count) const {
+    return AdjWork{psiC + count, tot + count,   C + count,
+                   prho + count, psimu + count, mu + count};
+  }
 };
 
 // Per-node adjoint intermediates: plane offsets in AdjBufs::a (N phases).
@@ -66,8 +79,18 @@ struct AdjBufs {
   double* ggpsi;
 };
 
-// One reverse step: from the stored state of level n and the adjoint of
-// level n + 1, the adjoint of level n, and the gradient sums updated.
+// The fields of `count` stored states, state_bytes apart, into `count` sets of
+// work fields, work_n values apart.
+template <class S>
+hipError_t launch_adj_fields(int nphase, const Coef<double>& kd,
+                             const AdjFwd<S>& fw, long long state_bytes,
+                             int count, const S* psi, const S* wet,
+                             const AdjWork& w, long long work_n,
+                             hipStream_t st);
+
+// One reverse step: from the stored state of level n, its fields w and the
+// adjoint of level n + 1, the adjoint of level n, and the gradient sums
+// updated.
 template <class S>
 hipError_t launch_adj_step(int nphase, const Coef<double>& kd,
                            const AdjFwd<S>& fw, const S* psi, const S* wet,

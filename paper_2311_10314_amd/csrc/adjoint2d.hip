@@ -15,7 +15,10 @@
 // Kernels of one reverse step:
 //   k_adj_fields  forward: phi C_i (pulled), their sum, C_i, phi rho; phi mu_i
 //                 (eq. 2.14) and mu_i = phi mu_i / psi_hat from C and psi in
-//                 LDS (a tile and its one-node halo)
+//                 LDS (a tile and its one-node halo). It needs no adjoint, so
+//                 one launch does a group of stored states (on a 256^2 box one
+//                 state alone is one workgroup per compute unit: 6.2 us for
+//                 one, 20 us for eight)
 //   k_adj_node    recomputes the node update at x and transposes it: the
 //                 adjoint of the pulled flow populations (complete, pushed to
 //                 x - c_p), of the pulled phase populations (direct part), of
@@ -31,7 +34,8 @@
 // reverse step adds where it reads the populations' adjoints, instead of being
 // added to 9 N planes here. One reverse step, 256^2 N = 2 (same GPU): five
 // kernels with a launch for each stage and the populations' planes read and
-// written twice 40 us, these three 30 us.
+// written twice 40 us; these three 30 us with the fields of one state at a
+// time, 25 us with eight and the kernels' tiles in XCD ranges.
 // The adjoint state and arithmetic are float64 for every context; the
 // forward states are read in the context's storage type (float32 contexts
 // are linearised about their own float32 trajectory).
@@ -148,6 +152,13 @@ constexpr int TX = 64, TY = 4, NT = TX * TY;
 constexpr int HX = TX + 2, HY = TY + 2, RING = HX * HY - NT;
 constexpr int kTileThreads = NT + (RING + 63) / 64 * 64;
 
+// Workgroup w runs on XCD w % 8: each XCD takes one contiguous range of the
+// work, so that the rows that neighbours share stay in one L2.
+__device__ inline unsigned xcd_range(unsigned w, unsigned total) {
+  const unsigned q = total / 8u, r = total % 8u, x = w % 8u, j = w / 8u;
+  return x < r ? x * (q + 1u) + j : r * (q + 1u) + (x - r) * q + j;
+}
+
 // What thread t works on: position (lx, ly) of the tile with its halo (own
 // nodes first), node idx of the box. on: the thread has a position; own: it is
 // a node of the tile inside the box.
@@ -160,7 +171,8 @@ __device__ inline TileNode tile_node(int nx, int ny) {
   TileNode t;
   const int tid = int(threadIdx.x);
   const unsigned gx = unsigned(nx + TX - 1) / TX;  // tiles per row
-  const int x0 = int(blockIdx.x % gx) * TX, y0 = int(blockIdx.x / gx) * TY;
+  const unsigned tile = xcd_range(blockIdx.x, gridDim.x);
+  const int x0 = int(tile % gx) * TX, y0 = int(tile / gx) * TY;
   t.on = true;
   t.own = false;
   if (tid < NT) {
@@ -199,7 +211,11 @@ __device__ inline P3<T> lds3(const T (&a)[HY][HX], int lx, int ly) {
 
 template <int N, class S>
 __global__ __launch_bounds__(kTileThreads) void k_adj_fields(
-    Coef<double> kd, AdjFwd<S> fw, const S* psi_f, const S* wet, AdjWork w) {
+    Coef<double> kd, AdjFwd<S> fw, long long state_bytes, const S* psi_f,
+    const S* wet, AdjWork w, long long work_n) {
+  // blockIdx.y: state of the group
+  fw = fw.after(blockIdx.y * state_bytes);
+  w = w.after(blockIdx.y * work_n);
   __shared__ double sC[N][HY][HX];
   __shared__ double sp[HY][HX];
   const long long n = kd.n;
@@ -297,7 +313,8 @@ __global__ __launch_bounds__(kThreads) void k_adj_node(Coef<double> kd,
                                                        AdjBufs<R> ab) {
   using D = double;
   const long long n = k.n;
-  const long long x = (long long)blockIdx.x * kThreads + threadIdx.x;
+  const long long x =
+      (long long)xcd_range(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
   if (x >= n) return;
   const int gx = int(x % k.nx), gy = int(x / k.nx);
   const Nb3 b = nb3(gx, gy, k.nx, k.ny);
@@ -918,13 +935,24 @@ inline unsigned blocks_for(long long n) {
 }
 
 template <int N, class S>
+hipError_t adj_fields_n(const Coef<double>& kd, const AdjFwd<S>& fw,
+                        long long state_bytes, int count, const S* psi,
+                        const S* wet, const AdjWork& w, long long work_n,
+                        hipStream_t st) {
+  const dim3 g(unsigned((kd.nx + TX - 1) / TX) * unsigned((kd.ny + TY - 1) / TY),
+               unsigned(count));
+  hipLaunchKernelGGL((k_adj_fields<N, S>), g, dim3(kTileThreads), 0, st, kd, fw,
+                     state_bytes, psi, wet, w, work_n);
+  return hipGetLastError();
+}
+
+template <int N, class S>
 hipError_t adj_step_n(const Coef<double>& kd, const AdjFwd<S>& fw,
                       const S* psi, const S* wet, const AdjWork& w,
                       const AdjBufs<double>& ab, hipStream_t st) {
   const dim3 g(blocks_for(kd.n)), t(kThreads);
   const dim3 gt(unsigned((kd.nx + TX - 1) / TX) * unsigned((kd.ny + TY - 1) / TY));
   const dim3 tt(kTileThreads);
-  hipLaunchKernelGGL((k_adj_fields<N, S>), gt, tt, 0, st, kd, fw, psi, wet, w);
   hipLaunchKernelGGL((k_adj_node<N, S, double>), g, t, 0, st, kd, kd, fw, psi,
                      w, ab);
   hipLaunchKernelGGL((k_adj_mid<N, S, double>), gt, tt, 0, st, kd, psi, wet, w,
@@ -933,6 +961,25 @@ hipError_t adj_step_n(const Coef<double>& kd, const AdjFwd<S>& fw,
 }
 
 }  // namespace
+
+template <class S>
+hipError_t launch_adj_fields(int nphase, const Coef<double>& kd,
+                             const AdjFwd<S>& fw, long long state_bytes,
+                             int count, const S* psi, const S* wet,
+                             const AdjWork& w, long long work_n,
+                             hipStream_t st) {
+  if (count < 1 || count > 65535) return hipErrorInvalidValue;
+  switch (nphase) {
+    case 2:
+      return adj_fields_n<2, S>(kd, fw, state_bytes, count, psi, wet, w, work_n, st);
+    case 3:
+      return adj_fields_n<3, S>(kd, fw, state_bytes, count, psi, wet, w, work_n, st);
+    case 4:
+      return adj_fields_n<4, S>(kd, fw, state_bytes, count, psi, wet, w, work_n, st);
+    default:
+      return hipErrorInvalidValue;
+  }
+}
 
 template <class S>
 hipError_t launch_adj_step(int nphase, const Coef<double>& kd,
@@ -986,6 +1033,9 @@ hipError_t launch_adj_finish(const Coef<double>& kd, int nm1, const S* psi,
 }
 
 #define DDCC_ADJ_INST(S)                                                       \
+  template hipError_t launch_adj_fields<S>(                                    \
+      int, const Coef<double>&, const AdjFwd<S>&, long long, int, const S*,    \
+      const S*, const AdjWork&, long long, hipStream_t);                       \
   template hipError_t launch_adj_step<S>(int, const Coef<double>&,            \
                                          const AdjFwd<S>&, const S*,          \
                                          const S*, const AdjWork&,            \

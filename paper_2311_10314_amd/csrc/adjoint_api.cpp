@@ -229,7 +229,12 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
   R* a = lT[1] + n;
   R* l = a + sal;
 
-  ACHK(work.alloc((size_t)(4 * N + 2) * n * sizeof(double)), "hipMalloc work");
+  // fields of a group of states at a time: up to 8 while they stay a few
+  // adjoint states (small boxes, where one state does not fill the chip)
+  const int64_t by_size = (int64_t)(size_t(1) << 19) / (int64_t)n;
+  const int64_t group = by_size < 1 ? 1 : (by_size > 8 ? 8 : by_size);
+  const size_t work_n = (size_t)(4 * N + 2) * n;
+  ACHK(work.alloc((size_t)group * work_n * sizeof(double)), "hipMalloc work");
   AdjWork w;
   w.psiC = work.as<double>();
   w.tot = w.psiC + (size_t)N * n;
@@ -322,7 +327,18 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
       ACHK(hipStreamWaitEvent(c->stream, pp.ready[b], 0), "event");
     const int64_t s0 = sg * interval;
     const int64_t s1 = s0 + interval < nsteps ? s0 + interval : nsteps;
+    int64_t have = s1;  // first state whose fields are in w
     for (int64_t s = s1 - 1; s >= s0; --s) {
+      if (s < have) {
+        have = s + 1 - s0 < group ? s0 : s + 1 - group;
+        ACHK(launch_adj_fields<S>(
+                 N, c->kd,
+                 view<S>(segbuf[b] + (size_t)(have - s0) * L.total, L),
+                 (long long)L.total, (int)(s + 1 - have),
+                 static_cast<const S*>(c->psi), static_cast<const S*>(c->wet),
+                 w, (long long)work_n, c->stream),
+             "adjoint field kernel");
+      }
       AdjBufs<R> ab;
       ab.lfB = lf[la];
       ab.lfA = lf[la ^ 1];
@@ -339,7 +355,9 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
       ACHK(launch_adj_step<S>(N, c->kd,
                               view<S>(segbuf[b] + (size_t)(s - s0) * L.total, L),
                               static_cast<const S*>(c->psi),
-                              static_cast<const S*>(c->wet), w, ab, c->stream),
+                              static_cast<const S*>(c->wet),
+                              w.after((s - have) * (int64_t)work_n), ab,
+                              c->stream),
            "adjoint step kernels");
       la ^= 1;
     }
