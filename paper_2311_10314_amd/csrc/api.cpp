@@ -33,6 +33,15 @@ size_t step_bytes(size_t pops, size_t T, size_t hist, size_t work) {
   return 2 * (pops + T + hist + work);
 }
 
+// Whether rows of nx populations start where nontemporal stores of a row's
+// 64-node pieces fill what they touch: on 64 bytes, or on 32 in FP64 (us per
+// step, nontemporal / plain: rows on 64 bytes, 2064 x 2048 N = 3 FP32 505 / 533;
+// on 32, 2056 x 2048 N = 3 FP32 521 / 462, 1500 x 1333 N = 2 FP64 290 / 293; on
+// less, MODE_RAGGED).
+bool rows_on_lines(long long nx, size_t bytes) {
+  return nx * bytes % (bytes == 8 ? 32 : 64) == 0;
+}
+
 int fail(ddcc_ctx* c, int code, const std::string& msg) {
   if (c) c->err = msg;
   return code;
@@ -331,7 +340,9 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
                      const double* inC, const double* inU, const double* inP,
                      double* oC, double* oU, double* oP) {
   Bufs<Pop, S> b = bufs<Pop, S>(c, mode);
-  if (mode == MODE_STEP && c->stream_stores) mode = MODE_STREAM;
+  if (mode == MODE_STEP && c->stream_stores)
+    mode = c->p.dim == 2 && !rows_on_lines(c->p.nx, sizeof(Pop)) ? MODE_RAGGED
+                                                                 : MODE_STREAM;
   b.inC = inC;
   b.inU = inU;
   b.inP = inP;
@@ -1368,7 +1379,11 @@ hipError_t batch_launch_as(ddcc_batch* b, const Coef<R>* k, int mode,
                            const double* inU, const double* inP, double* oC,
                            double* oU, double* oP, long long out_n) {
   Bufs<Pop, S> r = batch_bufs<Pop, S>(b, mode);
-  if (mode == MODE_STEP && b->stream_stores) mode = MODE_STREAM;
+  if (mode == MODE_STEP && b->stream_stores) {
+    mode = MODE_STREAM;
+    for (int nx : b->nx)
+      if (!rows_on_lines(nx, sizeof(Pop))) mode = MODE_RAGGED;
+  }
   r.inC = inC;
   r.inU = inU;
   r.inP = inP;

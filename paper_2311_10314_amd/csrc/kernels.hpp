@@ -11,6 +11,12 @@ namespace ddcc {
 // writes; the host picks it for grids whose step does not fit the 256 MB
 // memory-side cache (there it is 3-6 % faster; on cache-resident grids
 // plain stores are, by up to 19 %).
+// MODE_RAGGED (2D) is MODE_STREAM without nontemporal accesses, for grids
+// whose rows do not start on cache lines: a line there is written by two
+// wavefronts, and only the caches can join the two parts (us per step, same
+// GPU, nontemporal -> plain: 1500 x 1333 N = 2 FP32 193 -> 159, 1501 x 1333 N =
+// 3 FP32 275 -> 219, 2050 x 2048 N = 3 FP32 580 -> 471, 1500 x 1333 N = 2 FP64
+// 295 either way).
 // MODE_FORK (2D, FP64 and FP32) is MODE_STEP with the history read from
 // Bufs::histA, for steps from one stored state to another.
 enum {
@@ -18,7 +24,8 @@ enum {
   MODE_INIT = 1,
   MODE_MOMENTS = 2,
   MODE_STREAM = 3,
-  MODE_FORK = 4
+  MODE_FORK = 4,
+  MODE_RAGGED = 5
 };
 
 // Pointers handed to the step/init/moments kernels (by value).

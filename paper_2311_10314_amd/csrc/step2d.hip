@@ -332,7 +332,7 @@ struct Step2D {
   __device__ static inline void plain(Smem& sm, const Coef<D>& kd,
                                       const Coef<R>& k, const Bufs<Pop, S>& b,
                                       const Grid& gd, int x0, int y0) {
-    if constexpr (MODE == MODE_STREAM) {
+    if constexpr (MODE == MODE_STREAM || MODE == MODE_RAGGED) {
       body(sm, kd, k, b, gd, x0, y0);
       return;
     }
@@ -839,7 +839,7 @@ template <int N, class Pop, class S, class R, int MODE, int TY>
 __global__ __launch_bounds__(TX* TY) void k_step2d(
     const Coef<double>* __restrict__ kd, const Coef<R>* __restrict__ k,
     Bufs<Pop, S> b, Grid gd) {
-  if constexpr (MODE == MODE_STREAM)
+  if constexpr (MODE == MODE_STREAM || MODE == MODE_RAGGED)
     Step2D<N, Pop, S, R, MODE, TY>::run(*kd, *k, b,
                                         Grid{k->nx, k->ny, k->n, 0u});
   else
@@ -916,6 +916,8 @@ hipError_t launch_mode(int mode, const Coef<double>& kd, const Coef<R>& k,
       return launch_ty<N, Pop, S, R, MODE_STEP>(kd, k, b, ty, cus, st);
     case MODE_STREAM:
       return launch_ty<N, Pop, S, R, MODE_STREAM>(kd, k, b, ty, cus, st);
+    case MODE_RAGGED:
+      return launch_ty<N, Pop, S, R, MODE_RAGGED>(kd, k, b, ty, cus, st);
     case MODE_INIT:
       return launch_ty<N, Pop, S, R, MODE_INIT>(kd, k, b, ty, cus, st);
     case MODE_FORK:
@@ -976,6 +978,9 @@ hipError_t launch_batch_n(int mode, const Coef<double>* kd, const Coef<R>* k,
                        0, st, kd, k, b, tiles, insts, ntiles);
   else if (mode == MODE_STREAM)
     hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STREAM, TY>), g, blk,
+                       0, st, kd, k, b, tiles, insts, ntiles);
+  else if (mode == MODE_RAGGED)
+    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_RAGGED, TY>), g, blk,
                        0, st, kd, k, b, tiles, insts, ntiles);
   else
     hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STEP, TY>), g, blk, 0,

@@ -1,4 +1,4 @@
-"""Launch shapes of boxes that leave the chip partly idle, against the oracle.
+"""Launch shapes and step modes that the grid size chooses, against the oracle.
 
 2D boxes whose tiles fit the compute units run in wide workgroups (a thread
 per halo node): one-tile boxes, partial tiles in x and y, and the largest
@@ -94,3 +94,12 @@ def test_captured_steps_equal_single_steps(dim, shape, precision):
         assert np.array_equal(a.save(), b.save())
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("N,shape,precision", [(2, (830, 1001), "fp64"),
+                                               (3, (811, 801), "fp32"),
+                                               (4, (701, 699), "fp16")])
+def test_streaming_rows_off_cache_lines(N, shape, precision):
+    """2D boxes larger than the memory-side cache whose rows start anywhere:
+    streaming load order without nontemporal accesses, partial tiles."""
+    _check(W.random_small(2, N, shape, seed=46), precision, 2)
