@@ -2,6 +2,7 @@
 // derived constants, device buffers (A-B population pairs), kernel launches.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -242,14 +243,33 @@ void fourth_order_q(int lat, double d0, double q4[3][3]) {
   }
 }
 
+// Row pitch of the planes of a 3D box: rows padded to whole 128-byte lines of
+// every array they are in (32 nodes; 16 in FP64). Otherwise the pieces of a row
+// that wavefronts read and write start inside lines, which costs more than the
+// idle nodes' memory: us per step with three contexts at once, rows as they are
+// -> padded: 130 x 75 x 101 N = 3 D3Q7 FP32 227 -> 172, N = 2 D3Q15 FP32
+// 127 x 100 x 100 295 -> 200, 100^3 235 -> 186. The padding may take at most
+// 30 % of a larger box's memory (boxes of up to 2^22 nodes: any), and boxes
+// beyond 2^26 nodes, whose memory may be scarce, keep their rows.
+int row_pitch(const ddcc_params& p) {
+  if (p.dim != 3) return p.nx;
+  const long long unit = p.precision == DDCC_FP64 ? 16 : 32;
+  const long long px = (p.nx + unit - 1) / unit * unit;
+  const long long n = px * p.ny * p.nz;
+  const bool small = n <= (1LL << 22);
+  if (!small && (n > (1LL << 26) || 10 * px > 13 * (long long)p.nx)) return p.nx;
+  return (int)px;
+}
+
 template <class R>
-void fill_coef(const ddcc_params& p, long long n, Coef<R>& k) {
+void fill_coef(const ddcc_params& p, int px, long long n, Coef<R>& k) {
   std::memset(&k, 0, sizeof(k));
   const int N = p.nphase;
   const double cs2 = p.d0;
   k.nx = p.nx;
   k.ny = p.ny;
   k.nz = p.nz;
+  k.px = px;
   k.n = n;
   k.cs2 = R(cs2);
   k.inv_cs2 = R(1.0 / cs2);
@@ -349,7 +369,7 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
   b.outC = oC;
   b.outU = oU;
   b.outP = oP;
-  b.out_n = c->n;
+  b.out_n = c->nodes;
   if (c->p.dim == 2)
     return launch_2d<Pop, S, R>(c->p.nphase, mode, c->kd, k, b, c->tile_y,
                                 c->cus, c->stream);
@@ -377,7 +397,7 @@ hipError_t launch(ddcc_ctx* c, int mode, const double* inC, const double* inU,
 
 int ensure_staging(ddcc_ctx* c) {
   if (c->staging) return DDCC_OK;
-  const size_t count = (size_t)(c->p.nphase + c->p.dim + 1) * c->n;
+  const size_t count = (size_t)(c->p.nphase + c->p.dim + 1) * c->nodes;
   HIPCHK(c, hipMalloc(&c->staging, count * sizeof(double)), "hipMalloc staging");
   return DDCC_OK;
 }
@@ -550,6 +570,52 @@ int diag_reset(ddcc_ctx* c) {
   return DDCC_OK;
 }
 
+// The arrays of a checkpoint in its order; on the host their rows are nx nodes
+// long, on the device px.
+struct StatePart {
+  void* dev;
+  size_t planes, esz;
+};
+
+std::array<StatePart, 5> state_parts(ddcc_ctx* c) {
+  const size_t N = (size_t)c->p.nphase;
+  return {StatePart{c->f[c->cur], N * (size_t)(c->Qf - 1), c->pesz},
+          StatePart{c->f0[c->cur], N, sizeof(double)},
+          StatePart{c->g[c->cur], (size_t)c->Qg, c->pesz},
+          StatePart{c->hist, (size_t)c->nhist, c->esz},
+          StatePart{c->T[c->cur], (size_t)c->nT, c->esz}};
+}
+
+// Copy a part to the host (to) or from it. Padded rows go through the work
+// fields, which hold nothing between steps, as many planes at a time as fit
+// (the copy engine's own pitched copy of 248 MB took 3.1 s, this one 24 ms).
+hipError_t copy_part(ddcc_ctx* c, const StatePart& q, char* to,
+                     const char* from) {
+  const hipMemcpyKind kind = to ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice;
+  if (c->px == c->p.nx) {
+    const size_t bytes = q.planes * (size_t)c->n * q.esz;
+    if (to) return hipMemcpyAsync(to, q.dev, bytes, kind, c->stream);
+    return hipMemcpyAsync(q.dev, from, bytes, kind, c->stream);
+  }
+  const size_t fit = 2 * (size_t)c->p.nphase * sizeof(double) / q.esz;
+  for (size_t i = 0; i < q.planes; i += fit) {
+    const size_t m = q.planes - i < fit ? q.planes - i : fit;
+    const long long rows = (long long)m * c->p.ny * c->p.nz;
+    const size_t bytes = m * (size_t)c->nodes * q.esz;
+    const size_t at = i * (size_t)c->nodes * q.esz;
+    char* dev = static_cast<char*>(q.dev) + i * (size_t)c->n * q.esz;
+    hipError_t e = hipSuccess;
+    if (!to) e = hipMemcpyAsync(c->work, from + at, bytes, kind, c->stream);
+    if (e == hipSuccess)
+      e = launch_copy_rows(dev, c->work, to != nullptr, c->p.nx, c->px, rows,
+                           q.esz, c->stream);
+    if (e == hipSuccess && to)
+      e = hipMemcpyAsync(to + at, c->work, bytes, kind, c->stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct SaveHeader {
   char magic[8];
   int32_t dim, nx, ny, nz, nphase, lattice_f, lattice_g, precision;
@@ -622,7 +688,9 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   ddcc_ctx* c = new (std::nothrow) ddcc_ctx();
   if (!c) return DDCC_E_NOMEM;
   c->p = *p;
-  c->n = (long long)p->nx * p->ny * p->nz;
+  c->nodes = (long long)p->nx * p->ny * p->nz;
+  c->px = row_pitch(*p);
+  c->n = (long long)c->px * p->ny * p->nz;
   c->Qf = lattice_q(p->lattice_f);
   c->Qg = lattice_q(p->lattice_g);
   const int d = p->dim;
@@ -651,8 +719,8 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
     }
     c->own_stream = true;
   }
-  fill_coef<double>(c->p, c->n, c->kd);
-  fill_coef<float>(c->p, c->n, c->kf);
+  fill_coef<double>(c->p, c->px, c->n, c->kd);
+  fill_coef<float>(c->p, c->px, c->n, c->kf);
   const size_t n = (size_t)c->n;
   const size_t sf = (size_t)p->nphase * (c->Qf - 1) * n * c->pesz;
   const size_t sg = (size_t)c->Qg * n * c->pesz;
@@ -687,6 +755,14 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
     e = hipMemcpy(c->dkd, &c->kd, sizeof(Coef<double>), hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(c->dkf, &c->kf, sizeof(Coef<float>), hipMemcpyHostToDevice);
+  // no kernel touches the padding of the rows but the mass sums, which take
+  // it with the nodes
+  for (int a = 0; a < 2 && e == hipSuccess && c->px != p->nx; ++a) {
+    e = hipMemsetAsync(c->f[a], 0, sf, c->stream);
+    if (e == hipSuccess)
+      e = hipMemsetAsync(c->f0[a], 0, (size_t)p->nphase * n * sizeof(double),
+                         c->stream);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     release(c);
@@ -717,11 +793,11 @@ static int geometry_from_device(ddcc_ctx* c, int K, const double* psik,
   hipError_t e =
       c->p.precision == DDCC_FP64
           ? launch_wet_field<double>(psik, ctk, K, nm1, c->p.nx, c->p.ny,
-                                     c->p.nz, static_cast<double*>(c->psi),
+                                     c->p.nz, c->px, static_cast<double*>(c->psi),
                                      static_cast<double*>(c->wet), c->n, 0,
                                      c->stream)
           : launch_wet_field<float>(psik, ctk, K, nm1, c->p.nx, c->p.ny,
-                                    c->p.nz, static_cast<float*>(c->psi),
+                                    c->p.nz, c->px, static_cast<float*>(c->psi),
                                     static_cast<float*>(c->wet), c->n, 0,
                                     c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "geometry kernel");
@@ -758,7 +834,7 @@ static int check_walls(ddcc_ctx* c, int K, const double* psik,
   if (K < 1 || K > DDCC_MAX_WALLS)
     return fail(c, DDCC_E_INVAL, "number of walls must be in [1, 8]");
   if (!psik) return fail(c, DDCC_E_INVAL, "psi is NULL");
-  const size_t n = (size_t)c->n;
+  const size_t n = (size_t)c->nodes;
   for (size_t i = 0; i < (size_t)K * n; ++i)
     if (!(psik[i] >= 0.0 && psik[i] <= 1.0))
       return fail(c, DDCC_E_INVAL, "psi must be finite and in [0, 1]");
@@ -774,7 +850,7 @@ int ddcc_init_geometry_walls(ddcc_ctx* c, int nwalls, const double* psi,
   if (!c) return DDCC_E_INVAL;
   int rc = check_walls(c, nwalls, psi, cos_theta);
   if (rc) return rc;
-  const size_t n = (size_t)c->n, np = (size_t)nwalls * n;
+  const size_t n = (size_t)c->nodes, np = (size_t)nwalls * n;
   const size_t nc = cos_theta ? np * (c->p.nphase - 1) : 0;
   // Boxes of up to kKeepNodes nodes keep the staging memory that init_fields
   // uses too; larger ones, and walls that do not fit it, take their own for
@@ -783,7 +859,7 @@ int ddcc_init_geometry_walls(ddcc_ctx* c, int nwalls, const double* psi,
   // of 0.1 after other streams' work, 256^2.)
   constexpr long long kKeepNodes = 1 << 20;
   const size_t room = (size_t)(c->p.nphase + c->p.dim + 1) * n;
-  const bool keep = c->n <= kKeepNodes && np + nc <= room;
+  const bool keep = c->nodes <= kKeepNodes && np + nc <= room;
   double* d = nullptr;
   if (keep) {
     rc = ensure_staging(c);
@@ -833,7 +909,7 @@ int ddcc_init_fields(ddcc_ctx* c, const double* C, const double* u,
   if (!c) return DDCC_E_INVAL;
   if (!c->geom_ok) return fail(c, DDCC_E_STATE, "init_geometry first");
   if (!C) return fail(c, DDCC_E_INVAL, "C is NULL");
-  const size_t n = (size_t)c->n;
+  const size_t n = (size_t)c->nodes;
   const int N = c->p.nphase, d = c->p.dim;
   if (!all_finite(C, N * n) || (u && !all_finite(u, d * n)) ||
       (P && !all_finite(P, n)))
@@ -902,7 +978,7 @@ int ddcc_read_moments(ddcc_ctx* c, double* C, double* u, double* P) {
   if (!c->fields_ok) return fail(c, DDCC_E_STATE, "init_fields first");
   int rc = ensure_staging(c);
   if (rc) return rc;
-  const size_t n = (size_t)c->n;
+  const size_t n = (size_t)c->nodes;
   const int N = c->p.nphase, d = c->p.dim;
   double* sC = c->staging;
   double* sU = sC + N * n;
@@ -988,7 +1064,7 @@ int64_t ddcc_time(const ddcc_ctx* c) { return c ? c->t : -1; }
 int ddcc_save(ddcc_ctx* c, void* buf, size_t* bytes) {
   if (!c || !bytes) return fail(c, DDCC_E_INVAL, "NULL argument");
   if (!c->fields_ok) return fail(c, DDCC_E_STATE, "init_fields first");
-  const size_t n = (size_t)c->n;
+  const size_t n = (size_t)c->nodes;
   const size_t sf = (size_t)c->p.nphase * (c->Qf - 1) * n * c->pesz;
   const size_t sg = (size_t)c->Qg * n * c->pesz;
   const size_t sh = (size_t)c->nhist * n * c->esz;
@@ -1015,23 +1091,10 @@ int ddcc_save(ddcc_ctx* c, void* buf, size_t* bytes) {
   char* o = static_cast<char*>(buf);
   std::memcpy(o, &h, sizeof(h));
   o += sizeof(h);
-  HIPCHK(c, hipMemcpyAsync(o, c->f[c->cur], sf, hipMemcpyDeviceToHost, c->stream),
-         "save f");
-  o += sf;
-  HIPCHK(c, hipMemcpyAsync(o, c->f0[c->cur], s0, hipMemcpyDeviceToHost,
-                           c->stream),
-         "save f0");
-  o += s0;
-  HIPCHK(c, hipMemcpyAsync(o, c->g[c->cur], sg, hipMemcpyDeviceToHost, c->stream),
-         "save g");
-  o += sg;
-  HIPCHK(c, hipMemcpyAsync(o, c->hist, sh, hipMemcpyDeviceToHost, c->stream),
-         "save hist");
-  o += sh;
-  if (sT)
-    HIPCHK(c, hipMemcpyAsync(o, c->T[c->cur], sT, hipMemcpyDeviceToHost,
-                             c->stream),
-           "save T");
+  for (const StatePart& q : state_parts(c)) {
+    HIPCHK(c, copy_part(c, q, o, nullptr), "save state");
+    o += q.planes * n * q.esz;
+  }
   HIPCHK(c, hipStreamSynchronize(c->stream), "sync");
   *bytes = need;
   return DDCC_OK;
@@ -1040,7 +1103,7 @@ int ddcc_save(ddcc_ctx* c, void* buf, size_t* bytes) {
 int ddcc_load(ddcc_ctx* c, const void* buf, size_t bytes) {
   if (!c || !buf) return fail(c, DDCC_E_INVAL, "NULL argument");
   if (!c->geom_ok) return fail(c, DDCC_E_STATE, "init_geometry first");
-  const size_t n = (size_t)c->n;
+  const size_t n = (size_t)c->nodes;
   const size_t sf = (size_t)c->p.nphase * (c->Qf - 1) * n * c->pesz;
   const size_t sg = (size_t)c->Qg * n * c->pesz;
   const size_t sh = (size_t)c->nhist * n * c->esz;
@@ -1057,23 +1120,10 @@ int ddcc_load(ddcc_ctx* c, const void* buf, size_t bytes) {
       h.bytes != (int64_t)need)
     return fail(c, DDCC_E_INVAL, "checkpoint does not match this context");
   const char* s = static_cast<const char*>(buf) + sizeof(h);
-  HIPCHK(c, hipMemcpyAsync(c->f[c->cur], s, sf, hipMemcpyHostToDevice, c->stream),
-         "load f");
-  s += sf;
-  HIPCHK(c, hipMemcpyAsync(c->f0[c->cur], s, s0, hipMemcpyHostToDevice,
-                           c->stream),
-         "load f0");
-  s += s0;
-  HIPCHK(c, hipMemcpyAsync(c->g[c->cur], s, sg, hipMemcpyHostToDevice, c->stream),
-         "load g");
-  s += sg;
-  HIPCHK(c, hipMemcpyAsync(c->hist, s, sh, hipMemcpyHostToDevice, c->stream),
-         "load hist");
-  s += sh;
-  if (sT)
-    HIPCHK(c, hipMemcpyAsync(c->T[c->cur], s, sT, hipMemcpyHostToDevice,
-                             c->stream),
-           "load T");
+  for (const StatePart& q : state_parts(c)) {
+    HIPCHK(c, copy_part(c, q, nullptr, s), "load state");
+    s += q.planes * n * q.esz;
+  }
   HIPCHK(c, hipStreamSynchronize(c->stream), "sync");
   c->t = h.t;
   c->fields_ok = true;
@@ -1529,8 +1579,8 @@ int ddcc_batch_create(const ddcc_params* p, int count, const int* nx,
   }
   // kernel constants: plane stride ntot; the box sizes come per instance
   ddcc_params qs = q;
-  fill_coef<double>(qs, b->ntot, b->kd);
-  fill_coef<float>(qs, b->ntot, b->kf);
+  fill_coef<double>(qs, qs.nx, b->ntot, b->kd);
+  fill_coef<float>(qs, qs.nx, b->ntot, b->kf);
   const int N = q.nphase;
   const size_t nt = (size_t)b->ntot;
   hipError_t e = hipSuccess;
@@ -1605,8 +1655,8 @@ int ddcc_batch_set_params(ddcc_batch* b, int i, const ddcc_params* p) {
   if (rc != DDCC_OK) return bfail(b, rc, msg);
   Coef<double> kd;
   Coef<float> kf;
-  fill_coef<double>(q, b->ntot, kd);
-  fill_coef<float>(q, b->ntot, kf);
+  fill_coef<double>(q, q.nx, b->ntot, kd);
+  fill_coef<float>(q, q.nx, b->ntot, kf);
   // the tables are read by kernels on the batch stream
   if (hipStreamSynchronize(b->stream) != hipSuccess ||
       hipMemcpy(b->kds + i, &kd, sizeof(kd), hipMemcpyHostToDevice) !=
@@ -1643,12 +1693,12 @@ int ddcc_batch_init_geometry(ddcc_batch* b, int i, const double* psi,
   if (e == hipSuccess)
     e = b->p.precision == DDCC_FP64
             ? launch_wet_field<double>(d, nc ? d + n : nullptr, 1, N - 1,
-                                       b->nx[i], b->ny[i], 1,
+                                       b->nx[i], b->ny[i], 1, b->nx[i],
                                        static_cast<double*>(b->psi),
                                        static_cast<double*>(b->wet), b->ntot,
                                        b->off[i], b->stream)
             : launch_wet_field<float>(d, nc ? d + n : nullptr, 1, N - 1,
-                                      b->nx[i], b->ny[i], 1,
+                                      b->nx[i], b->ny[i], 1, b->nx[i],
                                       static_cast<float*>(b->psi),
                                       static_cast<float*>(b->wet), b->ntot,
                                       b->off[i], b->stream);

@@ -11,7 +11,8 @@ constexpr int kMaxN = 4;
 template <class R>
 struct Coef {
   int nx, ny, nz;
-  long long n;          // nodes (plane stride)
+  int px;               // row pitch of the planes (nx in 2D)
+  long long n;          // plane stride: px ny nz
   static constexpr unsigned off = 0;  // first node of the box in each plane
   R cs2, inv_cs2;       // c_s^2 = d0 (c = 1)
   R psi_min, lam, rho0;

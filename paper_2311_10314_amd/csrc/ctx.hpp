@@ -18,7 +18,9 @@ struct ddcc_ctx {
   bool own_stream = false;
   int device = 0;
   int cus = 0;  // compute units of the device
-  long long n = 0;
+  long long n = 0;      // plane stride: px ny nz
+  long long nodes = 0;  // nx ny nz
+  int px = 0;           // row pitch of the planes (row_pitch; nx in 2D)
   int Qf = 0, Qg = 0, nhist = 0, nT = 0;
   size_t esz = 8;   // history, T and geometry fields
   size_t pesz = 8;  // moving populations

@@ -122,13 +122,18 @@ hipError_t launch_2d_batch(int nphase, int mode, const Coef<double>* kd,
 // E_i = sum_k cos theta^k_iN |grad psi_k| (i < N-1), the gradient by the
 // fixed isotropic stencil (D2Q9 at nz = 1, else D3Q19) on the periodic
 // nx x ny x nz box. Inputs float64 on the device: psik [K][n], ctk
-// [K][N-1][n] (NULL: 90 degrees). Outputs in S at node off + x of planes of
-// plane_stride nodes.
+// [K][N-1][n] (NULL: 90 degrees). Outputs in S from node off on in planes of
+// plane_stride nodes with rows px apart.
 template <class S>
 hipError_t launch_wet_field(const double* psik, const double* ctk, int K,
-                            int nm1, int nx, int ny, int nz, S* psi_out,
-                            S* wet_out, long long plane_stride, long long off,
-                            hipStream_t st);
+                            int nm1, int nx, int ny, int nz, int px,
+                            S* psi_out, S* wet_out, long long plane_stride,
+                            long long off, hipStream_t st);
+
+// Copy rows of nx elements of esz (2, 4 or 8) bytes, px apart at `padded`, to
+// dense rows at `dense` (pack) or from them.
+hipError_t launch_copy_rows(void* padded, void* dense, bool pack, int nx,
+                            int px, long long rows, size_t esz, hipStream_t st);
 
 // Per-phase sums of all populations (rest plane f0 [N][stride_n] plus
 // the moving planes of f [N][Q-1][stride_n], nodes [0, n) of each plane) into

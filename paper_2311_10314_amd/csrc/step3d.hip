@@ -126,11 +126,11 @@ __device__ inline void sym_flux(R psi, const R* m, const R* u, R* Y) {
 // Periodic neighbourhood of node (x, y, z).
 struct Nbr3 {
   int xs[3], ys[3], zs[3];  // coordinate at offset -1, 0, +1
-  int nx, ny;
+  int px, ny;               // row pitch, rows per plane
   // node at x + (dx, dy, dz)
   __device__ inline unsigned at(int dx, int dy, int dz) const {
     return (unsigned(zs[dz + 1]) * unsigned(ny) + unsigned(ys[dy + 1])) *
-               unsigned(nx) +
+               unsigned(px) +
            unsigned(xs[dx + 1]);
   }
   // pull source of the population moving with c: x - c
@@ -139,9 +139,10 @@ struct Nbr3 {
   }
 };
 
-__device__ inline Nbr3 make_nbr3(int x, int y, int z, int nx, int ny, int nz) {
+__device__ inline Nbr3 make_nbr3(int x, int y, int z, int nx, int ny, int nz,
+                                 int px) {
   Nbr3 b;
-  b.nx = nx;
+  b.px = px;
   b.ny = ny;
   b.xs[1] = x;
   b.ys[1] = y;
@@ -153,6 +154,18 @@ __device__ inline Nbr3 make_nbr3(int x, int y, int z, int nx, int ny, int nz) {
   b.zs[0] = z == 0 ? nz - 1 : z - 1;
   b.zs[2] = z == nz - 1 ? 0 : z + 1;
   return b;
+}
+
+// Node (x, y, z) of the caller's arrays, whose rows are nx nodes long, and
+// their plane stride.
+template <class R>
+__device__ inline unsigned user_node(const Coef<R>& k, int x, int y, int z) {
+  return (unsigned(z) * unsigned(k.ny) + unsigned(y)) * unsigned(k.nx) +
+         unsigned(x);
+}
+template <class R>
+__device__ inline long long user_nodes(const Coef<R>& k) {
+  return (long long)k.nx * k.ny * k.nz;
 }
 
 template <class T, class S>
@@ -206,13 +219,14 @@ __global__ __launch_bounds__(TX* TY) void k_frac3d(Coef<double> k,
   constexpr int QF = LF::Q;
   int x, y, z;
   if (!node_of<TX, TY>(k.nx, k.ny, x, y, z)) return;
-  const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz);
+  const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz, k.px);
   const unsigned idx = nb.at(0, 0, 0);
   D psiC[N];
   if constexpr (MODE == MODE_INIT) {
     const D psi = D(ldp(b.psi, idx));
 #pragma unroll
-    for (int i = 0; i < N; ++i) psiC[i] = psi * ldp(b.inC + (long long)i * k.n, idx);
+    for (int i = 0; i < N; ++i) 
+      psiC[i] = psi * ldp(b.inC + (long long)i * user_nodes(k), user_node(k, x, y, z));
   } else {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -266,7 +280,7 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b,
     S p[HY][HX];
   };
   __shared__ Plane ring[3];
-  const int nx = k.nx, ny = k.ny, nz = k.nz;
+  const int nx = k.nx, ny = k.ny, nz = k.nz, px = k.px;
   // tile of this workgroup (per-plane XCD banding as in node_of)
   const unsigned gx = gridDim.x, per = gx * gridDim.y;
   unsigned bx = blockIdx.x, by = blockIdx.y;
@@ -288,7 +302,7 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b,
     for (int r = int(threadIdx.x); r < HN; r += TX * TY) {
       const int ly = r / HX, lx = r - ly * HX;
       const unsigned idx = (unsigned(zw) * unsigned(ny) +
-                            unsigned(wrap(y0 + ly - 1, ny))) * unsigned(nx) +
+                            unsigned(wrap(y0 + ly - 1, ny))) * unsigned(px) +
                            unsigned(wrap(x0 + lx - 1, nx));
       pl.p[ly][lx] = ldp(b.psi, idx);
 #pragma unroll
@@ -310,7 +324,7 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b,
       if (r < HN) {
         const int ly = r / HX, lx = r - ly * HX;
         const unsigned idx = (unsigned(zw) * unsigned(ny) +
-                              unsigned(wrap(y0 + ly - 1, ny))) * unsigned(nx) +
+                              unsigned(wrap(y0 + ly - 1, ny))) * unsigned(px) +
                              unsigned(wrap(x0 + lx - 1, nx));
         pre[u][N] = ldp(b.psi, idx);
 #pragma unroll
@@ -374,7 +388,7 @@ __global__ __launch_bounds__(TX* TY) void k_mu3d(Coef<double> k, Bufs<Pop, S> b,
       });
 #pragma unroll
       for (int j = 0; j < N; ++j) L[j] = D(1.0 / 6.0) * sf[j] + D(1.0 / 12.0) * se[j];
-      const unsigned idx = (unsigned(z) * unsigned(ny) + unsigned(y)) * unsigned(nx) +
+      const unsigned idx = (unsigned(z) * unsigned(ny) + unsigned(y)) * unsigned(px) +
                            unsigned(x);
       // wetting weights sum_k cos theta^k_jq |grad psi_k| from the stored
       // E_i = sum_k cos theta^k_iN |grad psi_k| (eq. 2.9 is linear in them)
@@ -456,12 +470,12 @@ struct NodeIn {
 
 template <int N, class LF, class LG, class Pop, class S, int MODE>
 __device__ inline void fetch_node(const Bufs<Pop, S>& b, long long n, int nx,
-                                  int ny, int nz, int x, int y, int z,
+                                  int ny, int nz, int px, int x, int y, int z,
                                   NodeIn<N, LF, LG, Pop, S>& in) {
   if constexpr (MODE != MODE_INIT) {
     constexpr bool NT = MODE == MODE_STREAM;
     constexpr int QF = LF::Q;
-    const Nbr3 nb = make_nbr3(x, y, z, nx, ny, nz);
+    const Nbr3 nb = make_nbr3(x, y, z, nx, ny, nz, px);
     const unsigned idx = nb.at(0, 0, 0);
     static_for<0, LG::Q>([&](auto pc) {
       constexpr int p = decltype(pc)::value;
@@ -499,7 +513,7 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
   using Pl = StepPlane<N, TX, TY>;
   constexpr int QF = LF::Q, QG = LG::Q;
   constexpr bool NT = MODE == MODE_STREAM;  // streaming stores
-  const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz);
+  const Nbr3 nb = make_nbr3(x, y, z, k.nx, k.ny, k.nz, k.px);
   const unsigned idx = nb.at(0, 0, 0);
   const long long n = k.n;
 
@@ -577,7 +591,8 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
   R sum_gm = R(0);
   if constexpr (MODE == MODE_INIT) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = b.inU ? R(ldp(b.inU + a * n, idx)) : R(0);
+    for (int a = 0; a < 3; ++a) 
+      u[a] = b.inU ? R(ldp(b.inU + a * user_nodes(k), user_node(k, x, y, z))) : R(0);
   } else {
     // -div T^{n-1}, T antisymmetric with components xy, xz, yz
     const Star<R> txy = gather<R>(b.TA, nb);
@@ -656,7 +671,7 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
                   psirho * u[1] * u[2] + Y[4], psirho * u[2] * u[2] + Y[5]};
   R psiP, P;
   if constexpr (MODE == MODE_INIT) {
-    P = b.inP ? R(ldp(b.inP, idx)) : R(0);
+    P = b.inP ? R(ldp(b.inP, user_node(k, x, y, z))) : R(0);
     psiP = psi * P;
   } else {
     // eq. (19)
@@ -670,10 +685,12 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
   }
   if constexpr (MODE == MODE_MOMENTS) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) stp<NT>(b.outC + i * n, idx, double(C[i]));
+    for (int i = 0; i < N; ++i)
+      stp<NT>(b.outC + i * user_nodes(k), user_node(k, x, y, z), double(C[i]));
 #pragma unroll
-    for (int a = 0; a < 3; ++a) stp<NT>(b.outU + a * n, idx, double(u[a]));
-    stp<NT>(b.outP, idx, double(P));
+    for (int a = 0; a < 3; ++a)
+      stp<NT>(b.outU + a * user_nodes(k), user_node(k, x, y, z), double(u[a]));
+    stp<NT>(b.outP, user_node(k, x, y, z), double(P));
     prefetch();
     return;
   }
@@ -718,7 +735,8 @@ __device__ inline void step3d_node(const Coef<double>& kd, const Coef<R>& k,
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     if constexpr (MODE == MODE_INIT) {
-      const D psiC = psi_d * ldp(b.inC + (long long)i * n, idx);
+      const D psiC =
+          psi_d * ldp(b.inC + (long long)i * user_nodes(k), user_node(k, x, y, z));
       const R X[3] = {R(psiC) * u[0], R(psiC) * u[1], R(psiC) * u[2]};
       const R em = k.eta[i] * psimu[i];
       D comp = D(0);
@@ -834,7 +852,7 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
   using Pl = StepPlane<N, TX, TY>;
   constexpr int HX = TX + 2, HY = TY + 2, HN = HX * HY;
   __shared__ Pl ring[3];
-  const int nx = k.nx, ny = k.ny, nz = k.nz;
+  const int nx = k.nx, ny = k.ny, nz = k.nz, px = k.px;
   const unsigned gx = gridDim.x, per = gx * gridDim.y;
   unsigned bx = blockIdx.x, by = blockIdx.y;
   if (per % 8u == 0u) {
@@ -855,7 +873,7 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
     for (int r = int(threadIdx.x); r < HN; r += TX * TY) {
       const int ly = r / HX, lx = r - ly * HX;
       const unsigned i0 = (unsigned(zw) * unsigned(ny) +
-                           unsigned(wrap(y0 + ly - 1, ny))) * unsigned(nx) +
+                           unsigned(wrap(y0 + ly - 1, ny))) * unsigned(px) +
                           unsigned(wrap(x0 + lx - 1, nx));
       pl.p[ly][lx] = double(ldp(b.psi, i0));
 #pragma unroll
@@ -893,7 +911,8 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
   constexpr bool RF = PF;
   In cur;
   if constexpr (PF)
-    if (own) fetch_node<N, LF, LG, Pop, S, MODE>(b, k.n, nx, ny, nz, x, y, z0, cur);
+    if (own) fetch_node<N, LF, LG, Pop, S, MODE>(b, k.n, nx, ny, nz, px, x, y, z0,
+                                                  cur);
   constexpr int PER = (HN + TX * TY - 1) / (TX * TY);  // ring slots per thread
   S pre[PER][2 * N + 1];
   auto fetch_ring = [&](int zz) {
@@ -904,7 +923,7 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
       if (r < HN) {
         const int ly = r / HX, lx = r - ly * HX;
         const unsigned i0 = (unsigned(zw) * unsigned(ny) +
-                             unsigned(wrap(y0 + ly - 1, ny))) * unsigned(nx) +
+                             unsigned(wrap(y0 + ly - 1, ny))) * unsigned(px) +
                             unsigned(wrap(x0 + lx - 1, nx));
         pre[u][2 * N] = ldp(b.psi, i0);
 #pragma unroll
@@ -951,7 +970,7 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
         step3d_node<N, LF, LG, Pop, S, R, MODE, TX, TY, true>(
             kd, k, b, x, y, z, pz, tx + 1, ty + 1, cur, [&] {
               if (more)
-                fetch_node<N, LF, LG, Pop, S, MODE>(b, k.n, nx, ny, nz, x, y,
+                fetch_node<N, LF, LG, Pop, S, MODE>(b, k.n, nx, ny, nz, px, x, y,
                                                     z + 1, cur);
             });
       } else {
@@ -982,7 +1001,8 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
 // every round is full and ZB stays). A shorter column has to promise 15 %:
 // other contexts' work may fill the idle units, and then the starts are what
 // is left (45 x 109 x 87 D3Q7 FP32, 8 -> 2 planes: alone 85 -> 75 us, three
-// contexts at once 61 -> 64).
+// contexts at once 61 -> 64). Boxes of odd width here and below: timed before
+// their rows were padded, both sides alike.
 inline int planes_per_group(int nz, int tiles, int slots, double start,
                             int least) {
   int best = ZB;

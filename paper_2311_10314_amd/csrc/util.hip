@@ -1,6 +1,7 @@
 // Reductions and conversions used by the host API.
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
 #include <mutex>
 #include <type_traits>
 
@@ -97,11 +98,27 @@ __global__ void k_convert(const double* src, S* dst, long long count) {
     dst[i] = S(src[i]);
 }
 
+// Rows of nx elements px apart at `padded` to or from dense rows. One element
+// per thread.
+template <class E, bool PACK>
+__global__ void k_copy_rows(E* padded, E* dense, int nx, int px,
+                            long long count) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  const long long row = i / nx;
+  const long long o = row * px + (i - row * nx);
+  if constexpr (PACK)
+    dense[i] = padded[o];
+  else
+    padded[o] = dense[i];
+}
+
 // Wetting weights of K walls (see launch_wet_field). One node per thread.
 template <class S>
 __global__ void k_wet_field(const double* psik, const double* ctk, int K,
-                            int nm1, int nx, int ny, int nz, S* psi_out,
-                            S* wet_out, long long stride, long long off) {
+                            int nm1, int nx, int ny, int nz, int px,
+                            S* psi_out, S* wet_out, long long stride,
+                            long long off) {
   const long long n = (long long)nx * ny * nz;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n) return;
@@ -136,8 +153,9 @@ __global__ void k_wet_field(const double* psik, const double* ctk, int K,
       E[i] += c * ag;
     }
   }
-  psi_out[off + idx] = S(ps);
-  for (int i = 0; i < nm1; ++i) wet_out[i * stride + off + idx] = S(E[i]);
+  const long long o = off + ((long long)z * ny + y) * px + x;
+  psi_out[o] = S(ps);
+  for (int i = 0; i < nm1; ++i) wet_out[i * stride + o] = S(E[i]);
 }
 
 // Per-phase totals from the per-block partials, summed in block order by
@@ -220,26 +238,60 @@ hipError_t launch_mass_finish(const double* partial, const int* bad, int nb,
   return hipGetLastError();
 }
 
+namespace {
+template <class E>
+hipError_t copy_rows_as(void* padded, void* dense, bool pack, int nx, int px,
+                        long long count, hipStream_t st) {
+  const dim3 grid((unsigned)((count + 255) / 256));
+  E* a = static_cast<E*>(padded);
+  E* b = static_cast<E*>(dense);
+  if (pack)
+    hipLaunchKernelGGL((k_copy_rows<E, true>), grid, dim3(256), 0, st, a, b, nx,
+                       px, count);
+  else
+    hipLaunchKernelGGL((k_copy_rows<E, false>), grid, dim3(256), 0, st, a, b,
+                       nx, px, count);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_copy_rows(void* padded, void* dense, bool pack, int nx,
+                            int px, long long rows, size_t esz,
+                            hipStream_t st) {
+  const long long count = rows * nx;
+  if (nx < 1 || px < nx || rows < 1 || (count + 255) / 256 > 0x7fffffffLL)
+    return hipErrorInvalidValue;
+  if (esz == 8)
+    return copy_rows_as<uint64_t>(padded, dense, pack, nx, px, count, st);
+  if (esz == 4)
+    return copy_rows_as<uint32_t>(padded, dense, pack, nx, px, count, st);
+  if (esz == 2)
+    return copy_rows_as<uint16_t>(padded, dense, pack, nx, px, count, st);
+  return hipErrorInvalidValue;
+}
+
 template <class S>
 hipError_t launch_wet_field(const double* psik, const double* ctk, int K,
-                            int nm1, int nx, int ny, int nz, S* psi_out,
-                            S* wet_out, long long plane_stride, long long off,
-                            hipStream_t st) {
+                            int nm1, int nx, int ny, int nz, int px,
+                            S* psi_out, S* wet_out, long long plane_stride,
+                            long long off, hipStream_t st) {
   const long long n = (long long)nx * ny * nz;
-  if (n <= 0 || K < 1 || nm1 < 0 || nm1 > kMaxN - 1) return hipErrorInvalidValue;
+  if (n <= 0 || px < nx || K < 1 || nm1 < 0 || nm1 > kMaxN - 1)
+    return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_wet_field<S>), dim3((unsigned)((n + 255) / 256)),
-                     dim3(256), 0, st, psik, ctk, K, nm1, nx, ny, nz, psi_out,
-                     wet_out, plane_stride, off);
+                     dim3(256), 0, st, psik, ctk, K, nm1, nx, ny, nz, px,
+                     psi_out, wet_out, plane_stride, off);
   return hipGetLastError();
 }
 
 template hipError_t launch_wet_field<double>(const double*, const double*, int,
-                                             int, int, int, int, double*,
+                                             int, int, int, int, int, double*,
                                              double*, long long, long long,
                                              hipStream_t);
 template hipError_t launch_wet_field<float>(const double*, const double*, int,
-                                            int, int, int, int, float*, float*,
-                                            long long, long long, hipStream_t);
+                                            int, int, int, int, int, float*,
+                                            float*, long long, long long,
+                                            hipStream_t);
 
 template <class S>
 hipError_t launch_mass(const double* f0, const S* f, int nphase, int Q,

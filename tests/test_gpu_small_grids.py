@@ -103,3 +103,43 @@ def test_streaming_rows_off_cache_lines(N, shape, precision):
     """2D boxes larger than the memory-side cache whose rows start anywhere:
     streaming load order without nontemporal accesses, partial tiles."""
     _check(W.random_small(2, N, shape, seed=46), precision, 2)
+
+
+@pytest.mark.parametrize("N,lattice,shape,precision",
+                         [(2, "D3Q15", (5, 3, 20), "fp64"),
+                          (3, "D3Q7", (7, 9, 33), "fp32"),
+                          (3, "D3Q15", (6, 5, 63), "fp16"),
+                          (2, "D3Q15", (3, 70, 97), "bf16"),
+                          (2, "D3Q15", (4, 6, 64), "fp32")])
+def test_rows_of_any_length_3d(N, lattice, shape, precision):
+    """Planes whose rows are padded on the device: a state moved between two
+    contexts through its dense checkpoint goes on bit for bit, and the mass is
+    the sum of the checkpoint's populations (float64 additions in another
+    order: each term is rounded once per addition at most)."""
+    from paper_2311_10314_amd.ddcc import Sim
+    prm = {"d0": 0.3} if lattice == "D3Q7" else {}
+    wl = W.random_small(3, N, shape, seed=47, lattice_f=lattice, **prm)
+    a, b = Sim.from_workload(wl, precision), Sim.from_workload(wl, precision)
+    a.step(3)
+    state = a.save()
+    b.load(state)
+    assert np.array_equal(b.save(), state)
+    for _ in range(2):
+        a.step(1)
+        b.step(1)
+        assert np.array_equal(a.save(), b.save())
+    assert all(np.array_equal(x, y)
+               for x, y in zip(a.read_moments(), b.read_moments()))
+    n, q = int(np.prod(shape)), 15 if lattice == "D3Q15" else 7
+    raw = a.save()[56:]
+    esz = {"fp64": 8, "fp32": 4}.get(precision, 2)
+    f = raw[:N * (q - 1) * n * esz].copy()
+    f = ((f.view(np.uint16).astype(np.uint32) << 16).view(np.float32)
+         if precision == "bf16" else f.view("f%d" % esz))
+    f0 = raw[f.size * esz:][:N * n * 8].copy().view(np.float64)
+    f = np.concatenate([f0.reshape(N, n),
+                        f.astype(np.float64).reshape(N, -1)], axis=1)
+    tol = 2 * n * q * 2.0 ** -53 * np.abs(f).sum(axis=1)
+    assert np.all(np.abs(a.mass() - f.sum(axis=1)) <= tol)
+    a.close()
+    b.close()
