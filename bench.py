@@ -57,17 +57,17 @@ PREC_BYTES = {"fp64": (8, 8), "fp32": (4, 4), "fp16": (2, 4), "bf16": (2, 4)}
 # launches: C_i from the pulled phase populations, the chemical potential,
 # the node update; the 16-bit instances appear under their mangled names).
 KERNEL_TAGS = {   # the 256^3 steps run in the streaming mode (3), 512^2 in 0
-    ("3d", "fp32"): ["k_frac3d<2, ddcc::D3Q15, float, float, float, 3, 4>",
-                     "k_mu3d<2, float, float, 4, true>",
+    ("3d", "fp32"): ["k_frac3d<2, ddcc::D3Q15, float, float, float, 3, 64, 4>",
+                     "k_mu3d<2, float, float, 64, 4, true>",
                      "k_step3d<2, ddcc::D3Q15, ddcc::D3Q19, float, float, "
-                     "float, 3, 4>"],
-    ("3d", "fp64"): ["k_frac3d<2, ddcc::D3Q15, double, double, double, 3, 4>",
-                     "k_mu3d<2, double, double, 4, true>",
+                     "float, 3, 64, 4>"],
+    ("3d", "fp64"): ["k_frac3d<2, ddcc::D3Q15, double, double, double, 3, 64, 4>",
+                     "k_mu3d<2, double, double, 64, 4, true>",
                      "k_step3d<2, ddcc::D3Q15, ddcc::D3Q19, double, double, "
-                     "double, 3, 4>"],
-    ("3d", "fp16"): ["k_frac3dILi2ENS_5D3Q15EDF16_ffLi3ELi4E",
-                     "k_mu3dILi2EDF16_fLi4ELb1E",
-                     "k_step3dILi2ENS_5D3Q15ENS_5D3Q19EDF16_ffLi3ELi4E"],
+                     "double, 3, 64, 4>"],
+    ("3d", "fp16"): ["k_frac3dILi2ENS_5D3Q15EDF16_ffLi3ELi64ELi4E",
+                     "k_mu3dILi2EDF16_fLi64ELi4ELb1E",
+                     "k_step3dILi2ENS_5D3Q15ENS_5D3Q19EDF16_ffLi3ELi64ELi4E"],
     ("2d", "fp32"): ["k_step2d<3, float, float, float, 0, 8>"],
     ("2d", "fp64"): ["k_step2d<3, double, double, double, 0, 4>"],
     ("2dhbm", "fp32"): ["k_step2d<3, float, float, float, 3, 8>"],
@@ -368,7 +368,7 @@ def gpu_errors(wl, precision, steps, ref, torch):
 def batched_leg(count, steps, torch, graph_steps=50):
     """Batched leg: `count` independent 2D N = 2 instances of uneven sizes
     (sides from {64, 96, 128, 192, 256}, seeded disks and droplets) advanced
-    by one persistent launch per step, the tile height picked by the
+    by one launch per step, the tile height picked by the
     library's autotuner and the steps replayed from HIP graphs of
     `graph_steps` steps. FP32."""
     import numpy as np
