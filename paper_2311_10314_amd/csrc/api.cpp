@@ -245,19 +245,23 @@ void fourth_order_q(int lat, double d0, double q4[3][3]) {
 
 // Row pitch of the planes of a 3D box: rows padded to whole 128-byte lines of
 // every array they are in (32 nodes; 16 in FP64). Otherwise the pieces of a row
-// that wavefronts read and write start inside lines, which costs more than the
-// idle nodes' memory: us per step with three contexts at once, rows as they are
-// -> padded: 130 x 75 x 101 N = 3 D3Q7 FP32 227 -> 172, N = 2 D3Q15 FP32
-// 127 x 100 x 100 295 -> 200, 100^3 235 -> 186. The padding may take at most
-// 30 % of a larger box's memory (boxes of up to 2^22 nodes: any), and boxes
-// beyond 2^26 nodes, whose memory may be scarce, keep their rows.
+// that wavefronts read and write start inside lines. us per step, rows as they
+// are -> padded, one context / each of three at once, boxes of about 700000
+// nodes: FP32 N = 2 75 nodes 193/174 -> 162/139, 100 162/155 -> 142/130, 130
+// 186/174 -> 148/132; FP64 70 330/320 -> 272/244, 100 267/239 -> 256/224; FP16
+// N = 3 130 238/228 -> 199/187. Not for rows that one tile spans (every line
+// is in one workgroup's hands, and padding is only more lines: 33 nodes FP32
+// 157/127 -> 175/155, 54 151/137 -> 148/144, 26 FP64 191/144 -> 204/178), nor
+// where the padding is more than 30 % of a row, 25 in the 16-bit storages (100
+// nodes FP16, 28 %, 107/101 -> 125/99). Boxes beyond 2^26 nodes, whose memory
+// may be scarce, keep their rows too.
 int row_pitch(const ddcc_params& p) {
-  if (p.dim != 3) return p.nx;
+  if (p.dim != 3 || p.nx <= 64) return p.nx;
+  const bool half = p.precision == DDCC_FP16 || p.precision == DDCC_BF16;
   const long long unit = p.precision == DDCC_FP64 ? 16 : 32;
   const long long px = (p.nx + unit - 1) / unit * unit;
-  const long long n = px * p.ny * p.nz;
-  const bool small = n <= (1LL << 22);
-  if (!small && (n > (1LL << 26) || 10 * px > 13 * (long long)p.nx)) return p.nx;
+  const long long most = (half ? 125 : 130) * (long long)p.nx / 100;
+  if (px > most || px * p.ny * p.nz > (1LL << 26)) return p.nx;
   return (int)px;
 }
 
