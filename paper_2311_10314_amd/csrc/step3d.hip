@@ -1067,11 +1067,19 @@ hipError_t launch_ty3(const Coef<double>& kd, const Coef<R>& k,
     return launch_3<N, LF, Pop, S, R, MODE, 64, 2>(kd, k, b, cus, st);
   // Boxes at most 32 nodes wide would leave half of every 64-node row idle:
   // 32 x 8 tiles there (same GPU, 24 x 150 x 100 FP32 96 -> 67 us per step).
-  // From 33 nodes on the rows are better kept long, even where 32 x 8 tiles
-  // have fewer idle nodes: 130 x 75 x 101 N = 3 D3Q7 FP32 248 -> 310 us, 80 x 90
-  // x 60 FP32 102 -> 103, 40 x 100 x 150 N = 3 FP64 318 -> 360.
+  // Wider ones take them in float64 where a row's last 64 nodes are at most half
+  // full, up to 160 nodes (a sixth of the work; one context / each of three at
+  // once, us per step: 80 x 90 x 60 218/149 -> 186/134, N = 3 292/205 ->
+  // 258/183, 66 x 60 x 64 137/108 -> 125/96, 80 x 160 x 160 786/710 ->
+  // 657/606, 96 x 90 x 64 236/170 -> 241/159, 96 x 40 x 40 59/54 -> 61/50,
+  // 130 x 75 x 101 N = 3 D3Q7 379/346 -> 371/315, 160 x 64 x 64 239/186 ->
+  // 242/181). In float the shorter rows take what the fewer idle nodes give:
+  // 130 x 75 x 101 N = 3 D3Q7 FP32 198/172 -> 204/171, 80 x 90 x 60 FP32 121/82
+  // -> 118/83, 110 x 100 x 90 N = 3 FP32 270/235 -> 271/233. 33 to 64 nodes
+  // have as many idle nodes either way: 40 x 100 x 150 N = 3 FP64 318 -> 360.
   if constexpr (MODE == MODE_STEP || MODE == MODE_STREAM) {
-    if (k.nx <= 32)
+    const bool half = sizeof(R) == 8 && k.nx <= 160 && (k.nx - 1) % 64 < 32;
+    if (k.nx <= 32 || half)
       return launch_3<N, LF, Pop, S, R, MODE, 32, 8>(kd, k, b, cus, st);
   }
   return launch_3<N, LF, Pop, S, R, MODE, 64, 4>(kd, k, b, cus, st);

@@ -61,6 +61,17 @@ def test_short_columns(N, lattice, shape, precision):
            precision, 3)
 
 
+@pytest.mark.parametrize("N,lattice,shape", [(2, "D3Q15", (9, 10, 65)),
+                                             (3, "D3Q7", (11, 17, 96)),
+                                             (2, "D3Q7", (6, 13, 129)),
+                                             (3, "D3Q15", (5, 8, 160))])
+def test_float64_rows_in_32_node_tiles(N, lattice, shape):
+    """Boxes several 32 x 8 tiles wide, the last one partly filled or full."""
+    prm = {"d0": 0.3} if lattice == "D3Q7" else {}
+    _check(W.random_small(3, N, shape, seed=48, lattice_f=lattice, **prm),
+           "fp64", 3)
+
+
 @pytest.mark.parametrize("lattice", ["D3Q15", "D3Q7"])
 def test_half_storage_three_phases(lattice):
     prm = {"d0": 0.3} if lattice == "D3Q7" else {}
@@ -110,7 +121,11 @@ def test_streaming_rows_off_cache_lines(N, shape, precision):
                           (3, "D3Q7", (7, 9, 33), "fp32"),
                           (3, "D3Q15", (6, 5, 63), "fp16"),
                           (2, "D3Q15", (3, 70, 97), "bf16"),
-                          (2, "D3Q15", (4, 6, 64), "fp32")])
+                          (2, "D3Q15", (4, 6, 64), "fp32"),
+                          (3, "D3Q7", (6, 5, 70), "fp64"),
+                          (2, "D3Q15", (5, 9, 100), "fp32"),
+                          (3, "D3Q15", (4, 7, 127), "fp16"),
+                          (2, "D3Q15", (3, 10, 130), "bf16")])
 def test_rows_of_any_length_3d(N, lattice, shape, precision):
     """Planes whose rows are padded on the device: a state moved between two
     contexts through its dense checkpoint goes on bit for bit, and the mass is
