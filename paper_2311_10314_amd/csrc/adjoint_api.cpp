@@ -46,8 +46,9 @@ struct Pipe {
     if (aux) (void)hipStreamSynchronize(aux);
   }
   hipError_t init(ddcc_ctx* c) {
-    hipError_t e = hipSuccess;
-    if (!c->adj_stream)
+    const detail::OnDevice on(c->device);
+    hipError_t e = on.status;
+    if (e == hipSuccess && !c->adj_stream)
       e = hipStreamCreateWithFlags(&c->adj_stream, hipStreamNonBlocking);
     for (hipEvent_t& ev : c->adj_events)
       if (e == hipSuccess && !ev)

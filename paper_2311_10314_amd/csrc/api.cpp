@@ -462,8 +462,9 @@ hipGraphExec_t step_graph(ddcc_ctx* c, int q) {
   // the calls below are allowed whatever else this thread captures
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  hipError_t e = hipSuccess;
-  if (!c->capture_stream)
+  const ddcc::detail::OnDevice on(c->device);
+  hipError_t e = on.status;
+  if (e == hipSuccess && !c->capture_stream)
     e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
   if (e == hipSuccess)
     e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeRelaxed);

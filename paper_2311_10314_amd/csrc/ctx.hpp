@@ -76,6 +76,29 @@ namespace ddcc::detail {
 int fail(ddcc_ctx* c, int code, const std::string& msg);
 // Record a HIP error (DDCC_E_NOMEM for out-of-memory, else DDCC_E_HIP).
 int hip_fail(ddcc_ctx* c, hipError_t e, const char* what);
+// Makes a device current for its scope. Streams, events and graphs belong to
+// the device that is current where they are made; those a context makes after
+// ddcc_create have to be on its own.
+class OnDevice {
+ public:
+  explicit OnDevice(int device) {
+    status = hipGetDevice(&before_);
+    if (status != hipSuccess || before_ == device) return;
+    status = hipSetDevice(device);
+    moved_ = status == hipSuccess;
+  }
+  ~OnDevice() {
+    if (moved_) (void)hipSetDevice(before_);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+  hipError_t status;
+
+ private:
+  int before_ = 0;
+  bool moved_ = false;
+};
+
 // Launch one forward step on the current buffers (the caller flips cur and
 // advances t).
 hipError_t step_launch(ddcc_ctx* c);

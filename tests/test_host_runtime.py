@@ -1,0 +1,125 @@
+"""The host side of the C ABI against a stand-in for the HIP runtime
+(tests/fake_hip.cpp, linked with the library's own objects): on which device
+streams and graphs are made, what is launched, what happens when the runtime
+refuses a call. No GPU is needed; kernels are recorded, not run."""
+import ctypes
+import glob
+import importlib.util
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2311_10314_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def fake_module(tmp_path_factory):
+    """The binding over the library's objects linked with the stand-in."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not available")
+    objs = [os.path.join(B.BUILD, os.path.splitext(s)[0] + ".o")
+            for s in B.SOURCES]
+    newest = max(os.path.getmtime(f)
+                 for f in glob.glob(os.path.join(B.CSRC, "*")))
+    if not all(os.path.exists(o) and os.path.getmtime(o) >= newest
+               for o in objs):
+        B.build()
+    d = tmp_path_factory.mktemp("fake")
+    obj = str(d / "fake_hip.o")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-fPIC",
+                    "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", obj], check=True)
+    # the stand-in's names are bound inside the library, whatever runtime
+    # this process has loaded
+    subprocess.run([gxx, "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o",
+                    str(d / "libddcc.so"), obj] + objs, check=True)
+    shutil.copy(os.path.join(os.path.dirname(B.LIB), "ddcc.py"),
+                str(d / "ddcc.py"))
+    spec = importlib.util.spec_from_file_location("ddcc_on_fake",
+                                                  str(d / "ddcc.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.LIB.fake_get.restype = ctypes.c_longlong
+    mod.LIB.fake_set.argtypes = [ctypes.c_char_p, ctypes.c_longlong]
+    return mod
+
+
+class Fake:
+    def __init__(self, mod):
+        self.d, self.lib = mod, mod.LIB
+
+    def set(self, key, value):
+        self.lib.fake_set(key.encode(), value)
+
+    def get(self, key):
+        return self.lib.fake_get(key.encode())
+
+    def launches(self, start=0):
+        """(kernel, grid, block, device of the stream, current device,
+        captured) of the launches from `start` on."""
+        out, name = [], ctypes.create_string_buffer(1024)
+        v = (ctypes.c_longlong * 9)()
+        for i in range(start, self.get("launches")):
+            self.lib.fake_launch(i, name, 1024, v)
+            out.append((name.value.decode(), tuple(v[:3]), tuple(v[3:6]),
+                        v[6], v[7], bool(v[8])))
+        return out
+
+    def sim(self, shape, N=2, precision="fp32", lattice="D3Q15"):
+        dim = len(shape)
+        prm = dict(d0=0.3) if lattice == "D3Q7" else {}
+        p = self.d.make_params(dim, shape, N,
+                               "D2Q9" if dim == 2 else lattice,
+                               "D2Q9" if dim == 2 else "D3Q19", precision,
+                               **prm)
+        s = self.d.Sim(p)
+        s.init_geometry(np.ones(shape))
+        C = np.zeros((N,) + tuple(shape))
+        C[0] = 1.0
+        s.init_fields(C)
+        return s
+
+
+@pytest.fixture
+def fake(fake_module):
+    fake_module.LIB.fake_reset()
+    f = Fake(fake_module)
+    yield f
+    fake_module.LIB.fake_reset()
+
+
+# ---- devices -----------------------------------------------------------------
+def test_captured_groups_are_made_on_the_contexts_device(fake):
+    """A context of device 1 stepped while device 0 is current: its captured
+    groups are recorded on a stream of device 1, with device 1 current, and
+    device 0 is current again afterwards."""
+    fake.lib.hipSetDevice(1)
+    s = fake.sim((40, 70))
+    fake.lib.hipSetDevice(0)
+    s.step(128)
+    s.step(200)
+    assert fake.get("graph_calls") > 0
+    captured = [x for x in fake.launches() if x[5]]
+    assert captured and all(x[3] == 1 and x[4] == 1 for x in captured)
+    assert fake.get("streams_on_0") == 0
+    assert fake.get("current") == 0
+    s.close()
+
+
+def test_adjoint_stream_is_made_on_the_contexts_device(fake):
+    fake.set("fill", 0x3f)      # the phase mass is not zero
+    fake.lib.hipSetDevice(1)
+    s = fake.sim((24, 70), precision="fp64")
+    fake.lib.hipSetDevice(0)
+    s.adjoint(6, 2, 0, np.ones((24, 70)))
+    assert fake.get("streams_on_1") == 2      # the context's own and this one
+    assert fake.get("streams_on_0") == 0 and fake.get("events_on_0") == 0
+    assert all(x[3] == 1 for x in fake.launches())
+    assert fake.get("current") == 0
+    s.close()
