@@ -429,12 +429,13 @@ constexpr int64_t kGraphLead = 8;
 constexpr int kGraphSteps[2] = {64, 16};  // even: cur keeps its parity
 
 void drop_step_graphs(ddcc_ctx* c) {
-  for (auto& by_parity : c->step_graph)
-    for (hipGraphExec_t& g : by_parity)
-      if (g) {
-        (void)hipGraphExecDestroy(g);
-        g = nullptr;
-      }
+  for (auto& by_size : c->step_graph)
+    for (auto& by_parity : by_size)
+      for (hipGraphExec_t& g : by_parity)
+        if (g) {
+          (void)hipGraphExecDestroy(g);
+          g = nullptr;
+        }
 }
 
 // Whether steps may be launched as groups now: a small box, past its first
@@ -449,15 +450,12 @@ bool graphs_usable(ddcc_ctx* c) {
 
 // The captured group of kGraphSteps[q] steps from the current parity, made on
 // a stream of the context's own (nothing else can be recorded there); nullptr
-// if that failed.
+// if that failed. A group stays until the context is destroyed, so nothing
+// here waits for the device, also after a change of the tile.
 hipGraphExec_t step_graph(ddcc_ctx* c, int q) {
-  if (c->graph_tile != c->tile_y) {
-    if (c->graph_tile && hipStreamSynchronize(c->stream) != hipSuccess)
-      return nullptr;
-    drop_step_graphs(c);
-    c->graph_tile = c->tile_y;
-  }
-  hipGraphExec_t& exec = c->step_graph[q][c->cur];
+  const int by_tile =
+      c->tile_y == 2 ? 0 : (c->tile_y == 4 ? 1 : (c->tile_y == 8 ? 2 : 3));
+  hipGraphExec_t& exec = c->step_graph[by_tile][q][c->cur];
   if (exec || c->graphs_failed) return exec;
   // the calls below are allowed whatever else this thread captures
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;

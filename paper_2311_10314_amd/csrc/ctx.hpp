@@ -56,10 +56,9 @@ struct ddcc_ctx {
   // sweep and kept (making and destroying them took 0.4 ms per sweep)
   hipStream_t adj_stream = nullptr;
   hipEvent_t adj_events[5] = {};
-  // Captured groups of steps of a small box (ddcc_step), by size and parity
-  // of cur, and the stream they are captured on.
-  hipGraphExec_t step_graph[2][2] = {};
-  int graph_tile = 0;  // tile_y they were captured with
+  // Captured groups of steps of a small box (ddcc_step), by tile height (2, 4,
+  // 8, 16), size and parity of cur, and the stream they are captured on.
+  hipGraphExec_t step_graph[4][2][2] = {};
   hipStream_t capture_stream = nullptr;
   int64_t direct_steps = 0;    // steps launched one by one so far
   bool graphs_failed = false;  // a capture failed: no further attempt

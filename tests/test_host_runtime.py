@@ -123,3 +123,40 @@ def test_adjoint_stream_is_made_on_the_contexts_device(fake):
     assert all(x[3] == 1 for x in fake.launches())
     assert fake.get("current") == 0
     s.close()
+
+
+# ---- captured groups of steps ------------------------------------------------
+def test_a_new_tile_does_not_make_step_wait(fake):
+    """ddcc_step enqueues and returns, also after a change of the tile: groups
+    in flight are neither waited for nor dropped, and the first tile's serve
+    again when it comes back."""
+    s = fake.sim((40, 70))
+    s.step(128)
+    s.step(200)
+    made, waits = fake.get("graphs"), fake.get("syncs")
+    s.set_tile(0, 8)
+    s.step(200)
+    other = fake.get("graphs")
+    assert other > made
+    s.set_tile(0, 2)
+    s.step(200)
+    assert fake.get("graphs") == other
+    assert fake.get("syncs") == waits
+    assert s.time == 728
+    s.close()
+    assert fake.get("graphs") == 0
+
+
+def test_a_new_tile_while_the_thread_captures_elsewhere(fake):
+    """The caller's thread records on a stream of its own meanwhile: ddcc_step
+    calls nothing that would break that recording."""
+    s = fake.sim((40, 70))
+    s.step(128)
+    s.step(200)
+    s.set_tile(0, 8)
+    fake.set("thread_captures", 1)
+    s.step(200)
+    assert fake.get("captures_broken") == 0
+    assert s.time == 528
+    fake.set("thread_captures", 0)
+    s.close()
