@@ -444,8 +444,11 @@ bool graphs_usable(ddcc_ctx* c) {
   if (c->n > kGraphNodes || c->graphs_failed || c->direct_steps < kGraphAfter)
     return false;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(c->stream, &st) == hipSuccess &&
-         st == hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();  // not the error of the launch that follows
+    return false;
+  }
+  return st == hipStreamCaptureStatusNone;
 }
 
 // The captured group of kGraphSteps[q] steps from the current parity, made on
@@ -503,11 +506,15 @@ hipError_t run_steps(ddcc_ctx* c, int64_t nsteps) {
       const hipGraphExec_t g =
           nsteps - s >= kGraphSteps[q] ? step_graph(c, q) : nullptr;
       if (g) {
-        const hipError_t e = hipGraphLaunch(g, c->stream);
-        if (e != hipSuccess) return e;
-        s += kGraphSteps[q];
-        c->t += kGraphSteps[q];
-        continue;
+        if (hipGraphLaunch(g, c->stream) == hipSuccess) {
+          s += kGraphSteps[q];
+          c->t += kGraphSteps[q];
+          continue;
+        }
+        // refused (a group's arguments take device memory): single launches,
+        // which report what is wrong if they fail too
+        (void)hipGetLastError();
+        c->graphs_failed = true;
       }
     }
     const hipError_t e = launch(c, MODE_STEP, nullptr, nullptr, nullptr,

@@ -1024,8 +1024,10 @@ int groups_per_cu(K* kernel, int threads) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &per_cu, reinterpret_cast<const void*>(kernel), threads, 0) !=
-      hipSuccess)
+      hipSuccess) {
+    (void)hipGetLastError();  // not the error of the launch that follows
     return 2;
+  }
   return per_cu < 1 ? 1 : per_cu;
 }
 

@@ -160,3 +160,28 @@ def test_a_new_tile_while_the_thread_captures_elsewhere(fake):
     assert s.time == 528
     fake.set("thread_captures", 0)
     s.close()
+
+
+@pytest.mark.parametrize("key,value", [("fail_is_capturing", 1),
+                                       ("fail_instantiate", 1),
+                                       ("fail_graph", 1), ("fail_graph", 2)])
+def test_steps_go_on_one_by_one_where_groups_are_refused(fake, key, value):
+    """Groups are a way of launching only: where the runtime refuses the query,
+    the group or its launch, the same steps are launched one by one, and the
+    refusal is not taken for an error of theirs."""
+    s = fake.sim((40, 70))
+    s.step(128)
+    before = fake.get("launches")
+    fake.set(key, value)
+    s.step(200)
+    assert s.time == 328
+    single = [x for x in fake.launches(before) if not x[5]]
+    assert len(single) + fake.get("graph_kernels") == 200
+    s.close()
+
+
+def test_occupancy_query_leaves_no_error_behind(fake):
+    fake.set("fail_occupancy", 1)
+    s = fake.sim((6, 8, 20), precision="fp16", lattice="D3Q7")
+    s.step(1)
+    s.close()
