@@ -278,9 +278,13 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
     ACHK(step_between<S>(c, from, s + 1 < nsteps ? from + L.total : fin, L,
                          c->stream),
          "step kernel");
-    ++c->t;
   }
-  if (nsteps > 0) ACHK(copy_state(c, fin, L, false), "final state");
+  // the context's own arrays are at level `last` until the final state is in
+  // them, and so is its time
+  if (nsteps > 0) {
+    ACHK(copy_state(c, fin, L, false), "final state");
+    c->t += nsteps - last;
+  }
 
   // objective on the final state
   double sw, sm;

@@ -185,3 +185,28 @@ def test_occupancy_query_leaves_no_error_behind(fake):
     s = fake.sim((6, 8, 20), precision="fp16", lattice="D3Q7")
     s.step(1)
     s.close()
+
+
+# ---- adjoint -------------------------------------------------------------------
+def test_a_failed_adjoint_leaves_time_with_the_state(fake):
+    """The last segment's forward steps are written to the sweep's own memory:
+    if one of them fails, or the first copy of the final state, the context
+    holds the level of that segment's checkpoint, and says so."""
+    fake.set("fill", 0x3f)
+    for failing, want in (("kernel", 4), ("copy", 4), ("none", 6)):
+        s = fake.sim((24, 70), precision="fp64")
+        if failing == "kernel":       # the sixth step from here
+            fake.set("fail_kernel", fake.get("kernel_calls") + 6)
+        elif failing == "copy":
+            # weights; populations, rest, g, history, T of the checkpoints of
+            # levels 0, 2 and 4; then the final state's
+            fake.set("fail_copy", fake.get("copies") + 1 + 3 * 5 + 1)
+        w = np.ones((24, 70))
+        if failing == "none":
+            s.adjoint(6, 2, 0, w)
+        else:
+            with pytest.raises(fake.d.DDCCError, match=(
+                    "step kernel" if failing == "kernel" else "final state")):
+                s.adjoint(6, 2, 0, w)
+        assert s.time == want, failing
+        s.close()
