@@ -48,7 +48,10 @@ int fail(ddcc_ctx* c, int code, const std::string& msg) {
   return code;
 }
 
+// The runtime keeps an error until it is read: reading it here keeps it out of
+// the check of a later kernel launch.
 int hip_fail(ddcc_ctx* c, hipError_t e, const char* what) {
+  (void)hipGetLastError();
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
   return fail(c, e == hipErrorOutOfMemory ? DDCC_E_NOMEM : DDCC_E_HIP, m);
 }
@@ -775,6 +778,7 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // see hip_fail
     release(c);
     delete c;
     return e == hipErrorOutOfMemory ? DDCC_E_NOMEM : DDCC_E_HIP;
@@ -1359,6 +1363,7 @@ int bfail(ddcc_batch* b, int code, const std::string& msg) {
 }
 
 int bhip(ddcc_batch* b, hipError_t e, const char* what) {
+  (void)hipGetLastError();  // see hip_fail
   return bfail(b, e == hipErrorOutOfMemory ? DDCC_E_NOMEM : DDCC_E_HIP,
                std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -1639,6 +1644,7 @@ int ddcc_batch_create(const ddcc_params* p, int count, const int* nx,
   // against 24.0), 64 x 8 for float
   if (e != hipSuccess ||
       build_tiles(b, q.precision == DDCC_FP64 ? 4 : 8) != DDCC_OK) {
+    (void)hipGetLastError();  // see hip_fail
     batch_release(b);
     delete b;
     return e == hipErrorOutOfMemory ? DDCC_E_NOMEM : DDCC_E_HIP;

@@ -210,3 +210,25 @@ def test_a_failed_adjoint_leaves_time_with_the_state(fake):
                 s.adjoint(6, 2, 0, w)
         assert s.time == want, failing
         s.close()
+
+
+# ---- errors ----------------------------------------------------------------------
+def test_an_error_is_reported_once(fake):
+    """A refused allocation or copy fails its call; the next calls, on this
+    context or another, launch their kernels as if it had not been."""
+    s = fake.sim((40, 70))
+    fake.set("fail_copy", fake.get("copies") + 1)
+    with pytest.raises(fake.d.DDCCError, match="copy"):
+        s.read_moments()
+    s.step(1)
+    fake.set("memory", fake.get("allocated") + 1000)
+    with pytest.raises(fake.d.DDCCError) as e:
+        fake.sim((40, 70))
+    assert e.value.code == fake.d.DDCC_E_NOMEM
+    s.step(1)
+    p = fake.d.make_params(2, (40, 70), 2, "D2Q9", "D2Q9", "fp32")
+    with pytest.raises(fake.d.DDCCError):
+        fake.d.Batch(p, [(40, 70), (30, 20)])
+    s.step(1)
+    fake.set("memory", 0)
+    s.close()
