@@ -969,23 +969,32 @@ hipError_t launch_batch_n(int mode, const Coef<double>* kd, const Coef<R>* k,
                           const Bufs<Pop, S>& b, const BatchTile* tiles,
                           const BatchInst* insts, unsigned ntiles,
                           hipStream_t st) {
-  const dim3 g(ntiles), blk(TX * TY);
-  if (mode == MODE_INIT)
-    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_INIT, TY>), g, blk, 0,
-                       st, kd, k, b, tiles, insts, ntiles);
-  else if (mode == MODE_MOMENTS)
-    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_MOMENTS, TY>), g, blk,
-                       0, st, kd, k, b, tiles, insts, ntiles);
-  else if (mode == MODE_STREAM)
-    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STREAM, TY>), g, blk,
-                       0, st, kd, k, b, tiles, insts, ntiles);
-  else if (mode == MODE_RAGGED)
-    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_RAGGED, TY>), g, blk,
-                       0, st, kd, k, b, tiles, insts, ntiles);
-  else
-    hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STEP, TY>), g, blk, 0,
-                       st, kd, k, b, tiles, insts, ntiles);
-  return hipGetLastError();
+  // A launch takes fewer than 2^32 threads: longer lists (tens of millions of
+  // tiles, most of them nearly empty) go in pieces.
+  constexpr unsigned most = (1u << 31) / (TX * TY);
+  const dim3 blk(TX * TY);
+  for (unsigned t = 0; t < ntiles; t += most, tiles += most) {
+    const unsigned m = min(most, ntiles - t);
+    const dim3 g(m);
+    if (mode == MODE_INIT)
+      hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_INIT, TY>), g, blk, 0,
+                         st, kd, k, b, tiles, insts, m);
+    else if (mode == MODE_MOMENTS)
+      hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_MOMENTS, TY>), g, blk,
+                         0, st, kd, k, b, tiles, insts, m);
+    else if (mode == MODE_STREAM)
+      hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STREAM, TY>), g, blk,
+                         0, st, kd, k, b, tiles, insts, m);
+    else if (mode == MODE_RAGGED)
+      hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_RAGGED, TY>), g, blk,
+                         0, st, kd, k, b, tiles, insts, m);
+    else
+      hipLaunchKernelGGL((k_step2d_batch<N, Pop, S, R, MODE_STEP, TY>), g, blk, 0,
+                         st, kd, k, b, tiles, insts, m);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace

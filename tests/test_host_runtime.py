@@ -232,3 +232,21 @@ def test_an_error_is_reported_once(fake):
     s.step(1)
     fake.set("memory", 0)
     s.close()
+
+
+# ---- batches -----------------------------------------------------------------------
+def test_a_batch_of_more_tiles_than_one_launch_takes(fake):
+    """One instance of 1 x 2^26 nodes has 2^23 tiles of 64 x 8, 2^32 threads,
+    which is more than a launch takes: every tile is launched once all the
+    same."""
+    ny = 1 << 26
+    p = fake.d.make_params(2, (ny, 1), 2, "D2Q9", "D2Q9", "fp32")
+    b = fake.d.Batch(p, [(ny, 1)])
+    b.init_geometry(0, np.zeros((ny, 1)))
+    b.init_fields(0, np.zeros((2, ny, 1)))
+    start = fake.get("launches")
+    b.step(1)
+    steps = fake.launches(start)
+    assert len(steps) > 1
+    assert sum(x[1][0] for x in steps) == ny // 8
+    b.close()
