@@ -692,17 +692,14 @@ int ddcc_default_params(ddcc_params* p) {
   return DDCC_OK;
 }
 
-int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
-  if (!out) return DDCC_E_INVAL;
-  *out = nullptr;
-  std::string msg;
-  int rc = validate(p, msg);
-  if (rc != DDCC_OK) return rc;
+// A context of validated parameters whose rows are px nodes apart.
+static int create_with_pitch(const ddcc_params* p, int px, void* stream,
+                             ddcc_ctx** out) {
   ddcc_ctx* c = new (std::nothrow) ddcc_ctx();
   if (!c) return DDCC_E_NOMEM;
   c->p = *p;
   c->nodes = (long long)p->nx * p->ny * p->nz;
-  c->px = row_pitch(*p);
+  c->px = px;
   c->n = (long long)c->px * p->ny * p->nz;
   c->Qf = lattice_q(p->lattice_f);
   c->Qg = lattice_q(p->lattice_g);
@@ -796,6 +793,20 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   }
   *out = c;
   return DDCC_OK;
+}
+
+int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
+  if (!out) return DDCC_E_INVAL;
+  *out = nullptr;
+  std::string msg;
+  int rc = validate(p, msg);
+  if (rc != DDCC_OK) return rc;
+  const int px = row_pitch(*p);
+  rc = create_with_pitch(p, px, stream, out);
+  // padded rows are for speed alone: where they do not fit, dense ones may
+  if (rc == DDCC_E_NOMEM && px != p->nx)
+    rc = create_with_pitch(p, p->nx, stream, out);
+  return rc;
 }
 
 // Geometry of K walls from float64 device arrays psik [K][n] and ctk

@@ -250,3 +250,26 @@ def test_a_batch_of_more_tiles_than_one_launch_takes(fake):
     assert len(steps) > 1
     assert sum(x[1][0] for x in steps) == ny // 8
     b.close()
+
+
+# ---- memory ------------------------------------------------------------------------
+def test_a_box_whose_padded_rows_do_not_fit_keeps_its_rows(fake):
+    """Rows of 100 FP32 nodes are padded to 128 on the device. With memory for
+    the dense box only, the context is made with dense rows; with less, it is
+    refused, and nothing is left behind."""
+    shape = (300, 200, 100)       # above the cache's size either way
+    s = fake.sim(shape)
+    padded = fake.get("allocated")
+    s.close()
+    assert fake.get("allocated") == 0
+    p = fake.d.make_params(3, shape, 2, "D3Q15", "D3Q19", "fp32")
+    dense = 100 * padded // 128   # and some small buffers
+    fake.set("memory", dense + (1 << 20))
+    s = fake.d.Sim(p)
+    assert 0 < fake.get("allocated") <= dense + (1 << 20)
+    s.close()
+    fake.set("memory", dense // 2)
+    with pytest.raises(fake.d.DDCCError) as e:
+        fake.d.Sim(p)
+    assert e.value.code == fake.d.DDCC_E_NOMEM
+    assert fake.get("allocated") == 0 and fake.get("streams") == 0
