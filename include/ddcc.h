@@ -243,10 +243,11 @@ int ddcc_diagnostics(ddcc_ctx* ctx, double* mass, int64_t* t_checked,
  * steps on the device), evaluates J, then sweeps back one segment of
  * `interval` steps at a time, recomputing the segment's states from its
  * checkpoint; the next segment is recomputed on a second stream of
- * default priority while the current one is swept. Device memory: about
- * (nsteps / interval + 2 interval + 1) states plus a few adjoint states,
- * released on return. On success the
- * context is left at the final level (time advanced by nsteps).
+ * default priority while the current one is swept (the stream stays with
+ * the context). Device memory: about (nsteps / interval + 2 interval) states
+ * (nsteps + 1 where interval >= nsteps) plus a few adjoint states, released
+ * on return. On success the context is left at the final level (time advanced
+ * by nsteps); after an error, at the level that ddcc_time tells.
  *
  * weight     host [ny][nx] float64, finite (the w above)
  * phase      k in [0, nphase)

@@ -209,14 +209,18 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
   const Layout L = state_layout(c);
   const int64_t nck = (nsteps + interval - 1) / interval;
   const int64_t seg = nsteps < interval ? nsteps : interval;
-  const size_t slots = (size_t)(nck + 2 * seg + 1);
+  // checkpoints of all segments but the last, whose first state goes straight
+  // into a segment buffer; the buffers; the final state
+  const int64_t nkept = nck > 0 ? nck - 1 : 0;
+  const size_t slots = (size_t)(nkept + (nck < 2 ? nck : 2) * seg + 1);
 
   DevMem store, adj, work, grads, misc;
   ACHK(store.alloc(slots * L.total), "hipMalloc checkpoints");
   auto slot = [&](size_t i) { return store.as<char>(i * L.total); };
   char* ck0 = slot(0);
-  char* segbuf[2] = {slot((size_t)nck), slot((size_t)(nck + seg))};
-  char* fin = slot((size_t)(nck + 2 * seg));
+  char* segbuf[2] = {slot((size_t)nkept), nck > 1 ? slot((size_t)(nkept + seg))
+                                                  : nullptr};
+  char* fin = slot(slots - 1);
 
   const size_t sfl = (size_t)N * 9 * n, sgl = 9 * n, shl = (size_t)c->nhist * n;
   const size_t sal = (size_t)adj_planes(N) * n;
@@ -265,7 +269,7 @@ int adjoint_as(ddcc_ctx* c, int64_t nsteps, int interval, int phase,
   // forward sweep: checkpoint every `interval` steps; the last segment, the
   // first that the reverse sweep needs, straight into its buffer
   int rc = DDCC_OK;
-  const int64_t last = nck > 0 ? (nck - 1) * interval : 0;
+  const int64_t last = nkept * interval;
   for (int64_t s = 0; s < last; ++s) {
     if (s % interval == 0)
       ACHK(copy_state(c, slot((size_t)(s / interval)), L, true), "checkpoint");

@@ -273,3 +273,25 @@ def test_a_box_whose_padded_rows_do_not_fit_keeps_its_rows(fake):
         fake.d.Sim(p)
     assert e.value.code == fake.d.DDCC_E_NOMEM
     assert fake.get("allocated") == 0 and fake.get("streams") == 0
+
+
+@pytest.mark.parametrize("nsteps,interval,states", [
+    (1, 1, 2), (2, 1, 4), (6, 2, 7), (5, 2, 7), (6, 6, 7), (6, 100, 7)])
+def test_adjoint_holds_no_state_it_does_not_use(fake, nsteps, interval, states):
+    """Stored states: a checkpoint for each segment but the last, two segment
+    buffers (one where there is one segment), the final state."""
+    fake.set("fill", 0x3f)
+    s = fake.sim((24, 70), precision="fp64")
+    def peak(n, k):
+        fake.set("peak", 0)
+        s.adjoint(n, k, 0, np.ones((24, 70)))
+        return fake.get("peak")
+    none = peak(0, 1)             # the final state alone
+    s.close()
+    # populations and rest populations, flow set, history and T of the sweep's
+    # slots: each a whole number of 256 bytes
+    n = 24 * 70 * 8
+    state = sum((x * n + 255) // 256 * 256 for x in (2 * 8, 2, 9, 8, 1))
+    s = fake.sim((24, 70), precision="fp64")
+    assert peak(nsteps, interval) - none == (states - 1) * state
+    s.close()
