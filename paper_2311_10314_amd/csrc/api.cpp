@@ -716,9 +716,8 @@ static int create_with_pitch(const ddcc_params* p, int px, void* stream,
     return DDCC_E_HIP;
   }
   // 3D: 64 x 4 columns
-  c->tile_y = d == 2 ? default_tile_2d(p->nx, p->ny, p->precision == DDCC_FP64,
-                                       c->cus)
-                     : 4;
+  c->tile_y =
+      d == 2 ? default_tile_2d(p->nx, p->ny, p->nphase, c->pesz, c->cus) : 4;
   c->tile_x = 64;
   if (stream) {
     c->stream = static_cast<hipStream_t>(stream);

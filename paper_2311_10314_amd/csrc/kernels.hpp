@@ -86,8 +86,9 @@ hipError_t launch_2d(int nphase, int mode, const Coef<double>& kd,
                      const Coef<R>& k, const Bufs<Pop, S>& b, int ty, int cus,
                      hipStream_t st);
 
-// Default tile height of launch_2d for a box.
-int default_tile_2d(int nx, int ny, bool fp64, int cus);
+// Default tile height of launch_2d for a box; pop_bytes: size of the population
+// type.
+int default_tile_2d(int nx, int ny, int nphase, size_t pop_bytes, int cus);
 
 // lattice_f: the phase-set lattice id (D3Q15 or D3Q7 of lattice.hpp); cus:
 // compute units of the device.

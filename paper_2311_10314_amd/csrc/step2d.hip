@@ -822,10 +822,16 @@ struct Step2D {
 // Whether a step in 64 x ty tiles takes wide workgroups (Step2D::wide): the
 // tiles fit the compute units, one each. 64 x 4 tiles only in float
 // arithmetic: the nine waves of a float64 one are all that its 156 registers
-// leave room for on a compute unit.
-bool wide_tiles(int nx, int ny, bool fp64, int ty, int cus) {
-  if (ty != 2 && !(ty == 4 && !fp64)) return false;
-  return (long long)((nx + TX - 1) / TX) * ((ny + ty - 1) / ty) <= cus;
+// leave room for on a compute unit. Those of four phases in 16-bit storage (130
+// registers, three waves per SIMD) fill a compute unit too and leave nothing
+// for other contexts' work: up to two thirds of the units (N = 4 FP16, us per
+// step, one box / each of three at once, plain 64 x 8 -> wide 64 x 4: 150 tiles
+// 13.8/6.8 -> 10.2/6.3, 180 14.2/7.1 -> 10.5/7.1, 220 14.6/7.1 -> 10.7/8.3, 256
+// 14.2/7.5 -> 10.7/9.9; N = 3 FP16 240 tiles 11.3/5.6 -> 9.1/5.4).
+bool wide_tiles(int nx, int ny, int nphase, size_t pop_bytes, int ty, int cus) {
+  if (ty != 2 && !(ty == 4 && pop_bytes < 8)) return false;
+  const int most = ty == 4 && nphase == 4 && pop_bytes == 2 ? cus * 2 / 3 : cus;
+  return (long long)((nx + TX - 1) / TX) * ((ny + ty - 1) / ty) <= most;
 }
 
 // kd, k: the context's coefficients in device memory. Passed by value the
@@ -866,7 +872,7 @@ hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
   if (!dk || !dr) return hipErrorInvalidValue;
   const Grid gd{k.nx, k.ny, k.n, 0u};
   if constexpr (MODE == MODE_STEP || MODE == MODE_FORK) {
-    if (wide_tiles(k.nx, k.ny, sizeof(R) == 8, ty, cus)) {
+    if (wide_tiles(k.nx, k.ny, N, sizeof(Pop), ty, cus)) {
       const dim3 g((k.nx + TX - 1) / TX, (k.ny + ty - 1) / ty);
       if (ty == 2)
         hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 2>), g,
@@ -1005,9 +1011,10 @@ hipError_t launch_batch_n(int mode, const Coef<double>* kd, const Coef<R>* k,
 // lower tiles that those come in: 64 x 2 while they fill at most half the
 // chip, then 64 x 4 (96 x 70 FP32 6.6 against 6.9 us, 256^2 FP32 8.9 against
 // 8.0 us with 64 x 4).
-int default_tile_2d(int nx, int ny, bool fp64, int cus) {
-  if (wide_tiles(nx, ny, fp64, 2, fp64 ? cus : cus / 2)) return 2;
-  if (wide_tiles(nx, ny, fp64, 4, cus)) return 4;
+int default_tile_2d(int nx, int ny, int nphase, size_t pop_bytes, int cus) {
+  const bool fp64 = pop_bytes == 8;
+  if (wide_tiles(nx, ny, nphase, pop_bytes, 2, fp64 ? cus : cus / 2)) return 2;
+  if (wide_tiles(nx, ny, nphase, pop_bytes, 4, cus)) return 4;
   return fp64 ? 4 : 8;
 }
 

@@ -295,3 +295,26 @@ def test_adjoint_holds_no_state_it_does_not_use(fake, nsteps, interval, states):
     s = fake.sim((24, 70), precision="fp64")
     assert peak(nsteps, interval) - none == (states - 1) * state
     s.close()
+
+
+# ---- launch shapes -------------------------------------------------------------------
+def _step_kernel(fake, shape, N, precision, lattice="D3Q15", tile=0):
+    """Name and workgroup size of the last kernel of a step."""
+    s = fake.sim(shape, N, precision, lattice)
+    s.set_tile(0, tile)
+    s.step(1)
+    name, _, block = fake.launches(fake.get("launches") - 1)[0][:3]
+    s.close()
+    return name, block[0]
+
+
+@pytest.mark.parametrize("N,precision,ny,wide", [
+    (4, "fp16", 160, True), (4, "fp16", 180, False), (4, "bf16", 256, False),
+    (4, "fp32", 256, True), (3, "fp16", 256, True), (2, "bf16", 257, False)])
+def test_wide_workgroups_of_four_phases_leave_room(fake, N, precision, ny,
+                                                   wide):
+    """256 nodes wide, 256 compute units: 64 x 4 tiles in wide workgroups while
+    they are at most 256, and 170 for four phases in 16-bit storage."""
+    name, block = _step_kernel(fake, (ny, 256), N, precision)
+    assert ("k_step2d_wide" in name) == wide
+    assert block == (576 if wide else 512)
