@@ -246,6 +246,29 @@ void fourth_order_q(int lat, double d0, double q4[3][3]) {
   }
 }
 
+int hist_planes(const ddcc_params& p) {
+  // 2D: phi C_i u (2N), Y (3), P; 3D: phi C_i (N), u (3), m^C (3), P (1)
+  return p.dim == 2 ? 2 * p.nphase + 4 : p.nphase + 7;
+}
+
+size_t pop_bytes(const ddcc_params& p) {
+  return p.precision == DDCC_FP64 ? 8 : (p.precision == DDCC_FP32 ? 4 : 2);
+}
+
+size_t field_bytes(const ddcc_params& p) {
+  return p.precision == DDCC_FP64 ? 8 : 4;
+}
+
+// step_bytes of a box whose planes hold n values.
+size_t step_bytes_of(const ddcc_params& p, size_t n) {
+  const size_t N = (size_t)p.nphase, d = (size_t)p.dim, e = field_bytes(p);
+  return step_bytes((N * (lattice_q(p.lattice_f) - 1) + lattice_q(p.lattice_g)) *
+                            n * pop_bytes(p) +
+                        N * n * sizeof(double),
+                    d * (d - 1) / 2 * n * e, hist_planes(p) * n * e,
+                    d == 3 ? 2 * N * n * e : 0);
+}
+
 // Row pitch of the planes of a 3D box: rows padded to whole 128-byte lines of
 // every array they are in (32 nodes; 16 in FP64). Otherwise the pieces of a row
 // that wavefronts read and write start inside lines. us per step, rows as they
@@ -257,7 +280,12 @@ void fourth_order_q(int lat, double d0, double q4[3][3]) {
 // 157/127 -> 175/155, 54 151/137 -> 148/144, 26 FP64 191/144 -> 204/178), nor
 // where the padding is more than 30 % of a row, 25 in the 16-bit storages (100
 // nodes FP16, 28 %, 107/101 -> 125/99). Boxes beyond 2^26 nodes, whose memory
-// may be scarce, keep their rows too.
+// may be scarce, keep their rows too, and so do boxes whose step would leave the
+// memory-side cache with its padding, or nearly (one context / each of three at
+// once: 130 x 90 x 42 FP32 N = 2 119/104 -> 128/93, 110 x 110 x 37 86/82 ->
+// 103/74, 80 x 110 x 36 N = 3, 0.97 of the cache with its padding, 77/86 ->
+// 86/90, 80 x 110 x 79 FP16 118/107 -> 138/108; at 0.75 of the cache 150 x 100 x
+// 25 FP32 84/77 -> 80/70).
 int row_pitch(const ddcc_params& p) {
   if (p.dim != 3 || p.nx <= 64) return p.nx;
   const bool half = p.precision == DDCC_FP16 || p.precision == DDCC_BF16;
@@ -265,6 +293,10 @@ int row_pitch(const ddcc_params& p) {
   const long long px = (p.nx + unit - 1) / unit * unit;
   const long long most = (half ? 125 : 130) * (long long)p.nx / 100;
   if (px > most || px * p.ny * p.nz > (1LL << 26)) return p.nx;
+  const size_t rows = (size_t)p.ny * p.nz;
+  if (step_bytes_of(p, rows * p.nx) <= kCacheBytes &&
+      step_bytes_of(p, rows * px) > kCacheBytes / 8 * 7)
+    return p.nx;
   return (int)px;
 }
 
@@ -707,8 +739,8 @@ static int create_with_pitch(const ddcc_params* p, int px, void* stream,
   // 2D: phi C_i u (2N), Y (3), P; 3D: phi C_i (N), u (3), m^C (3), P
   c->nhist = d == 2 ? 2 * p->nphase + 4 : p->nphase + 7;
   c->nT = d * (d - 1) / 2;
-  c->esz = p->precision == DDCC_FP64 ? 8 : 4;
-  c->pesz = p->precision == DDCC_FP64 ? 8 : (p->precision == DDCC_FP32 ? 4 : 2);
+  c->esz = field_bytes(*p);
+  c->pesz = pop_bytes(*p);
   if (hipGetDevice(&c->device) != hipSuccess ||
       hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount,
                             c->device) != hipSuccess) {
@@ -743,10 +775,7 @@ static int create_with_pitch(const ddcc_params* p, int px, void* stream,
     if (e == hipSuccess) e = hipMalloc(&c->T[a], sT);
   }
   if (e == hipSuccess) e = hipMalloc(&c->hist, (size_t)c->nhist * n * c->esz);
-  c->stream_stores =
-      step_bytes(sf + sg + (size_t)p->nphase * n * sizeof(double), sT,
-                 (size_t)c->nhist * n * c->esz,
-                 d == 3 ? (size_t)2 * p->nphase * n * c->esz : 0) > kCacheBytes;
+  c->stream_stores = step_bytes_of(*p, n) > kCacheBytes;
   if (e == hipSuccess) e = hipMalloc(&c->psi, n * c->esz);
   if (e == hipSuccess)
     e = hipMalloc(&c->wet, (size_t)(p->nphase - 1) * n * c->esz);

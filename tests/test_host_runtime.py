@@ -318,3 +318,25 @@ def test_wide_workgroups_of_four_phases_leave_room(fake, N, precision, ny,
     name, block = _step_kernel(fake, (ny, 256), N, precision)
     assert ("k_step2d_wide" in name) == wide
     assert block == (576 if wide else 512)
+
+
+@pytest.mark.parametrize("N,precision,shape,pitch", [
+    (2, "fp32", (42, 90, 130), 130),    # 0.98 of the cache dense, 1.21 padded
+    (3, "fp32", (36, 110, 80), 80),     # 0.81, 0.97
+    (2, "fp16", (79, 110, 80), 80),     # 0.90, 1.08
+    (2, "fp32", (25, 100, 150), 160),   # 0.75, 0.80
+    (2, "fp32", (63, 110, 100), 128),   # 1.38, 1.77
+    (2, "fp64", (48, 110, 130), 144)])  # 2.8, 3.1
+def test_rows_are_padded_where_the_cache_holds_them_or_neither(
+        fake, N, precision, shape, pitch):
+    """Device memory of the context: the planes are pitch nodes wide."""
+    def allocated(width):
+        p = fake.d.make_params(3, shape[:2] + (width,), N, "D3Q15", "D3Q19",
+                               precision)
+        s = fake.d.Sim(p)
+        n = fake.get("allocated")
+        s.close()
+        return n
+    # 64 nodes a row are never padded
+    per_row_node = allocated(64) / 64.0
+    assert abs(allocated(shape[2]) / per_row_node - pitch) < 0.5
