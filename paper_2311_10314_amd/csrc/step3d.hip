@@ -1061,27 +1061,43 @@ hipError_t launch_3(const Coef<double>& kd, const Coef<R>& k,
   return hipGetLastError();
 }
 
+// Whether the steps of a box take 32 x 8 tiles where 64 x 4 are the default.
+// Boxes at most 32 nodes wide do: 64-node rows would leave half of their lanes
+// idle (same GPU, 24 x 150 x 100 FP32 96 -> 67 us per step). Wider ones only in
+// float64, where a row's last 64 nodes are at most half full (us per step, 64 x
+// 4 -> 32 x 8 tiles, one context / each of three at once):
+// - up to 72 and from 129 to 160 nodes (65 x 40 x 40 72/49 -> 61/43, 72 x 90 x
+//   64 244/156 -> 224/142, 129 x 60 x 90 264/241 -> 263/229, 132 x 160 x 100 N = 3
+//   1019/988 -> 981/906, 160 x 90 x 64 312/267 -> 291/261; the least gain of 36
+//   boxes alone is 0.4 % under zero, 160 x 160 x 100);
+// - 73 to 96 nodes, three tiles instead of two, where the 64 x 4 columns are more
+//   than two per compute unit (96 x 110 x 79 293/273 -> 279/234, 88 x 100 x 100
+//   325/283 -> 292/266, 80 x 160 x 100 473/442 -> 406/368), or where the shorter
+//   list of whole columns ends a layer of the chip earlier (96 x 90 x 60 229/159
+//   -> 198/148). Elsewhere there one context alone is 2 to 4 % slower (96 x 90 x
+//   64 236 -> 240, 88 x 100 x 80 263 -> 268, 96 x 40 x 40 60 -> 62).
+// In float the shorter rows take what the fewer idle nodes give: 130 x 75 x 101
+// N = 3 D3Q7 FP32 198/172 -> 204/171, 80 x 90 x 60 FP32 121/82 -> 118/83, 110 x
+// 100 x 90 N = 3 FP32 270/235 -> 271/233. 33 to 64 nodes have as many idle nodes
+// either way: 40 x 100 x 150 N = 3 FP64 318 -> 360.
+bool narrow_tiles(int nx, int ny, int nz, bool fp64, int cus) {
+  if (nx <= 32) return true;
+  if (!fp64 || nx > 160 || (nx - 1) % 64 >= 32) return false;
+  if (nx <= 72 || nx > 96) return true;
+  const long long wide = 2LL * ((ny + 3) / 4), narrow = 3LL * ((ny + 7) / 8);
+  const auto layers = [cus](long long columns) { return (columns + cus - 1) / cus; };
+  return wide * ((nz + ZB - 1) / ZB) > 2LL * cus ||
+         layers(narrow * (nz / ZB)) < layers(wide * (nz / ZB));
+}
+
 template <int N, class LF, class Pop, class S, class R, int MODE>
 hipError_t launch_ty3(const Coef<double>& kd, const Coef<R>& k,
                       const Bufs<Pop, S>& b, int ty, int cus,
                       hipStream_t st) {
   if (ty == 2)
     return launch_3<N, LF, Pop, S, R, MODE, 64, 2>(kd, k, b, cus, st);
-  // Boxes at most 32 nodes wide would leave half of every 64-node row idle:
-  // 32 x 8 tiles there (same GPU, 24 x 150 x 100 FP32 96 -> 67 us per step).
-  // Wider ones take them in float64 where a row's last 64 nodes are at most half
-  // full, up to 160 nodes (a sixth of the work; one context / each of three at
-  // once, us per step: 80 x 90 x 60 218/149 -> 186/134, N = 3 292/205 ->
-  // 258/183, 66 x 60 x 64 137/108 -> 125/96, 80 x 160 x 160 786/710 ->
-  // 657/606, 96 x 90 x 64 236/170 -> 241/159, 96 x 40 x 40 59/54 -> 61/50,
-  // 130 x 75 x 101 N = 3 D3Q7 379/346 -> 371/315, 160 x 64 x 64 239/186 ->
-  // 242/181). In float the shorter rows take what the fewer idle nodes give:
-  // 130 x 75 x 101 N = 3 D3Q7 FP32 198/172 -> 204/171, 80 x 90 x 60 FP32 121/82
-  // -> 118/83, 110 x 100 x 90 N = 3 FP32 270/235 -> 271/233. 33 to 64 nodes
-  // have as many idle nodes either way: 40 x 100 x 150 N = 3 FP64 318 -> 360.
   if constexpr (MODE == MODE_STEP || MODE == MODE_STREAM) {
-    const bool half = sizeof(R) == 8 && k.nx <= 160 && (k.nx - 1) % 64 < 32;
-    if (k.nx <= 32 || half)
+    if (narrow_tiles(k.nx, k.ny, k.nz, sizeof(R) == 8, cus))
       return launch_3<N, LF, Pop, S, R, MODE, 32, 8>(kd, k, b, cus, st);
   }
   return launch_3<N, LF, Pop, S, R, MODE, 64, 4>(kd, k, b, cus, st);

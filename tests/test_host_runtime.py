@@ -340,3 +340,20 @@ def test_rows_are_padded_where_the_cache_holds_them_or_neither(
     # 64 nodes a row are never padded
     per_row_node = allocated(64) / 64.0
     assert abs(allocated(shape[2]) / per_row_node - pitch) < 0.5
+
+
+@pytest.mark.parametrize("precision,shape,tile,narrow", [
+    ("fp64", (90, 60, 65), 0, True), ("fp64", (64, 90, 72), 0, True),
+    ("fp64", (64, 90, 96), 0, False), ("fp64", (80, 100, 88), 0, False),
+    ("fp64", (40, 40, 96), 0, False), ("fp64", (60, 90, 96), 0, True),
+    ("fp64", (79, 110, 96), 0, True), ("fp64", (100, 160, 80), 4, True),
+    ("fp64", (90, 60, 97), 0, False), ("fp64", (90, 60, 129), 0, True),
+    ("fp64", (90, 60, 160), 0, True), ("fp64", (90, 60, 161), 0, False),
+    ("fp32", (90, 60, 65), 0, False), ("fp32", (20, 20, 32), 0, True),
+    ("fp64", (90, 60, 65), 2, False)])
+def test_shape_of_3d_tiles(fake, precision, shape, tile, narrow):
+    """32 x 8 instead of 64 x 4 tiles (256 compute units); 64 x 2 as asked."""
+    name, block = _step_kernel(fake, shape, 2, precision, tile=tile)
+    want = "32, 8>" if narrow else "64, %d>" % (tile or 4)
+    assert "k_step3d" in name and want in name.split("(ddcc::Coef")[0]
+    assert block == (128 if tile == 2 else 256)
