@@ -863,10 +863,11 @@ k_step2d_wide(const Coef<double>* __restrict__ kd,
   // An XCD's workgroups go to its four shader engines in turn, so with two or
   // four tiles per row one engine gets every last tile of the rows, and where
   // those hold a few nodes only, the step takes up to half as long again. The
-  // columns are turned by a quarter of a turn of the engines per row (us per
-  // step, same GPU: 200 x 250 FP32 64 x 4 10.7 -> 7.8, plain 64 x 8 9.5; N = 3
-  // FP16 14.1 -> 9.0, plain 12.9; full rows, 256^2 FP32, 8.0 either way; three
-  // tiles per row are spread as they are, and lose 5 % when turned).
+  // columns are turned from row to row instead, so that each engine gets its
+  // share of them (us per step, same GPU: 200 x 250 FP32 64 x 4 10.7 -> 7.8,
+  // plain 64 x 8 9.5; N = 3 FP16 14.1 -> 8.9, plain 12.9; 66 x 400 FP32 10.3 ->
+  // 7.9, plain 9.0; 70 x 96 64 x 2 7.7 -> 6.8; full rows, 256^2 FP32, 8.0 either
+  // way; three tiles per row, spread as they are, lose up to 5 % when turned).
   const unsigned gx = gridDim.x;
   if (gx == 2 || gx == 4) {
     const unsigned row = unsigned(y0) / TY, turn = gx == 4 ? row : row / 2;
@@ -957,11 +958,15 @@ hipError_t launch_mode(int mode, const Coef<double>& kd, const Coef<R>& k,
 // spread them over all XCDs and spent the counter's latency on every tile.
 // us per step, same GPU, queue -> direct: 256 instances N = 2 FP32 378 -> 349,
 // 128 FP64 374 -> 335 (64 x 4 tiles), 60 instances of 50 to 130 nodes a side N =
-// 3 FP32 65 -> 47, 10 of 120^2 FP32 18.6 -> 15.0. Chunks of 32 to 1400 entries
-// are within 2 %.) kds / ks: the coefficients of each instance (per-instance
+// 3 FP32 65 -> 47, 10 of 120^2 FP32 18.6 -> 15.0.) The chunk is not a power of
+// two: with 256 entries the XCDs work at addresses a power of two apart where
+// the instances' sizes are, and so on the same channels of the memory (300
+// instances of 128^2 N = 2 FP16 queue 267, 256 entries 271, 248 entries 249 us
+// per step, 1000 of them 900 -> 828, FP32 305 -> 290; on other sizes 96 to 300
+// entries are within 2 %). kds / ks: the coefficients of each instance (per-instance
 // parameters), read where they are used with the instance index of the tile,
 // which is uniform, so the reads are scalar.
-constexpr unsigned kBatchChunk = 256;
+constexpr unsigned kBatchChunk = 248;
 template <int N, class Pop, class S, class R, int MODE, int TY>
 __global__ __launch_bounds__(TX* TY) void k_step2d_batch(
     const Coef<double>* __restrict__ kds, const Coef<R>* __restrict__ ks,
