@@ -408,10 +408,11 @@ hipError_t launch_as(ddcc_ctx* c, const Coef<R>& k, int mode,
   b.outC = oC;
   b.outU = oU;
   b.outP = oP;
-  b.out_n = c->nodes;
-  if (c->p.dim == 2)
+  if (c->p.dim == 2) {
+    b.out_n = c->nodes;
     return launch_2d<Pop, S, R>(c->p.nphase, mode, c->kd, k, b, c->tile_y,
                                 c->cus, c->stream);
+  }
   return launch_3d<Pop, S, R>(c->p.nphase, c->p.lattice_f, mode, c->kd, k, b,
                               c->tile_x, c->tile_y, c->cus, c->stream);
 }

@@ -13,7 +13,6 @@ struct Coef {
   int nx, ny, nz;
   int px;               // row pitch of the planes (nx in 2D)
   long long n;          // plane stride: px ny nz
-  static constexpr unsigned off = 0;  // first node of the box in each plane
   R cs2, inv_cs2;       // c_s^2 = d0 (c = 1)
   R psi_min, lam, rho0;
   R m0;

@@ -53,8 +53,8 @@ struct Bufs {
   const double* inC;
   const double* inU;
   const double* inP;
-  // moments: plane i of C at outC + i * out_n, of u likewise (2D; in 3D the
-  // plane stride is n)
+  // moments: plane i of C at outC + i * out_n, of u likewise (2D; the 3D
+  // planes of in* and out* are dense, nx ny nz nodes)
   double* outC;
   double* outU;
   double* outP;

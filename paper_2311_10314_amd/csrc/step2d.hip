@@ -90,9 +90,7 @@ __device__ inline Patch<R> patch(const R (&a)[H][W], int x, int y) {
 
 // Box a tile belongs to: nx x ny nodes starting at node `off` of planes of
 // n nodes (one box: off = 0, n = nx ny; an instance of a batch: its offset in
-// planes that hold every instance). The single-box kernel passes its Coef for
-// the halo stages (same members nx, ny, n and off = 0), so the sizes stay
-// kernel arguments there.
+// planes that hold every instance).
 struct Grid {
   int nx, ny;
   long long n;
@@ -176,15 +174,14 @@ struct Step2D {
   // Kept: the pulled moving populations (own node) are written to `keep`
   // and handed on to phase 3 in registers instead of being loaded again.
   using Keep = R[N][Q];
-  template <bool KEPT = false, class G>
+  template <bool KEPT = false>
   __device__ static inline void node1(Smem& sm, const Coef<D>& k,
-                                      const Bufs<Pop, S>& b, const G& gd, int x0,
-                                      int y0, int lx,
-                                      int ly, D* psiC_out, Keep* keep = nullptr) {
+                                      const Bufs<Pop, S>& b, const Grid& gd,
+                                      int x0, int y0, int lx, int ly,
+                                      D* psiC_out, Keep* keep = nullptr) {
     const int gx = wrap(x0 + lx - 2, gd.nx), gy = wrap(y0 + ly - 2, gd.ny);
     const unsigned idx = gd.off + unsigned(gy * gd.nx + gx);
     const D psi = D(ldp(b.psi, idx));
-    D rho = D(0);
     if constexpr (MODE == MODE_INIT) {
 #pragma unroll
       for (int i = 0; i < N; ++i) psiC_out[i] = psi * ldp(b.inC + (long long)(i) * gd.n, idx);
@@ -207,15 +204,21 @@ struct Step2D {
         psiC_out[i] = ldp(b.f0A + (long long)(i) * gd.n, idx) + D(mv);
       }
     }
+    fractions(sm, k, psi, psiC_out, lx, ly);
+  }
+
+  // C_i, psi and phi rho of a C-region node from its phi C_i.
+  __device__ static inline void fractions(Smem& sm, const Coef<D>& k, D psi,
+                                          const D* psiC, int lx, int ly) {
     // C_i = phi C_i / sum_j phi C_j: equal to phi C_i / phi while the
     // constraint sum_j C_j = 1 of Section 2.1 holds, and keeps it exact.
-    D tot = D(0);
+    D tot = D(0), rho = D(0);
 #pragma unroll
-    for (int i = 0; i < N; ++i) tot += psiC_out[i];
+    for (int i = 0; i < N; ++i) tot += psiC[i];
     const D inv = D(1) / (tot > k.psi_min ? tot : k.psi_min);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const D C = psiC_out[i] * inv;
+      const D C = psiC[i] * inv;
       sm.C[i][ly][lx] = C;
       rho += k.rho[i] * C;
     }
@@ -225,9 +228,8 @@ struct Step2D {
 
   // Phase-2 inputs from global memory, issued in phase 1: the lagged T
   // into LDS and the wetting weights E_i into registers.
-  template <class G>
   __device__ static inline void load2(Smem& sm, const Bufs<Pop, S>& b,
-                                      const G& gd, int x0, int y0, int mx,
+                                      const Grid& gd, int x0, int y0, int mx,
                                       int my, S* E) {
     const int gx = wrap(x0 + mx - 1, gd.nx), gy = wrap(y0 + my - 1, gd.ny);
     const unsigned idx = gd.off + unsigned(gy * gd.nx + gx);
@@ -237,12 +239,11 @@ struct Step2D {
   }
 
   // Phase 2 at mu-region coordinates (mx, my): phi mu_i (eq. 2.14).
-  template <bool PRE2 = false, class G>
+  template <bool PRE2 = false>
   __device__ static inline void node2(Smem& sm, const Coef<D>& k,
-                                      const Bufs<Pop, S>& b, const G& gd, int x0,
-                                      int y0, int mx,
-                                      int my, D* psimu_out,
-                                      const S* E = nullptr) {
+                                      const Bufs<Pop, S>& b, const Grid& gd,
+                                      int x0, int y0, int mx, int my,
+                                      D* psimu_out, const S* E = nullptr) {
     const int lx = mx + 1, ly = my + 1;
     const int gx = wrap(x0 + mx - 1, gd.nx), gy = wrap(y0 + my - 1, gd.ny);
     const unsigned idx = gd.off + unsigned(gy * gd.nx + gx);
@@ -450,8 +451,6 @@ struct Step2D {
   // Phase 1 from loaded inputs (the arithmetic of node1).
   __device__ static inline void calc1(Smem& sm, const Coef<D>& k, const In1& in,
                                       int lx, int ly, D* psiC_out) {
-    const D psi = D(in.psi);
-    D rho = D(0);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       R mv = R(0);
@@ -459,18 +458,7 @@ struct Step2D {
       for (int p = 1; p < Q; ++p) mv += R(in.f[i][p - 1]);
       psiC_out[i] = in.f0[i] + D(mv);
     }
-    D tot = D(0);
-#pragma unroll
-    for (int i = 0; i < N; ++i) tot += psiC_out[i];
-    const D inv = D(1) / (tot > k.psi_min ? tot : k.psi_min);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const D C = psiC_out[i] * inv;
-      sm.C[i][ly][lx] = C;
-      rho += k.rho[i] * C;
-    }
-    sm.psi[ly][lx] = psi;
-    sm.prho[ly][lx] = psi * rho;
+    fractions(sm, k, D(in.psi), psiC_out, lx, ly);
   }
 
   // One tile by a wide workgroup of WT threads: NT for the tile's nodes, the
