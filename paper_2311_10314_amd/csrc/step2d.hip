@@ -879,7 +879,7 @@ hipError_t launch_ty(const Coef<double>& kd, const Coef<R>& k,
         hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 2>), g,
                            dim3(Step2D<N, Pop, S, R, MODE, 2>::WT), 0, st, dk,
                            dr, b, gd);
-      else
+      else if constexpr (sizeof(Pop) < 8)  // 64 x 4 in float only
         hipLaunchKernelGGL((k_step2d_wide<N, Pop, S, R, MODE, 4>), g,
                            dim3(Step2D<N, Pop, S, R, MODE, 4>::WT), 0, st, dk,
                            dr, b, gd);

@@ -357,3 +357,14 @@ def test_shape_of_3d_tiles(fake, precision, shape, tile, narrow):
     want = "32, 8>" if narrow else "64, %d>" % (tile or 4)
     assert "k_step3d" in name and want in name.split("(ddcc::Coef")[0]
     assert block == (128 if tile == 2 else 256)
+
+
+def test_no_wide_kernel_is_built_that_nothing_launches(fake):
+    name, wide = ctypes.create_string_buffer(1024), []
+    for i in range(fake.lib.fake_kernel_count()):
+        fake.lib.fake_kernel_name(i, name, 1024)
+        if b"k_step2d_wide<" in name.value:
+            wide.append(name.value.decode().split(">(")[0].split("<")[1])
+    assert len(wide) > 0
+    assert not [w for w in wide if "double, double, double" in w
+                and w.endswith(", 4")]
