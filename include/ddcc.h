@@ -119,13 +119,20 @@ int ddcc_default_params(ddcc_params* p);
 /* Validates *p and allocates the device state on the current HIP device.
  * `stream` is a hipStream_t to run on (e.g. a torch stream), or NULL for a
  * stream the context creates and owns. On success *out holds a new context;
- * on failure *out is NULL and the return code says why. */
+ * on failure *out is NULL and the return code says why. 3D boxes of more than
+ * 64 nodes a row may keep their rows padded to whole cache lines on the
+ * device: up to 30 % more device memory, and dense rows where that does not
+ * fit. Arrays that cross this ABI, and checkpoints, are dense. */
 int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out);
 
 /* Static geometry (eq. 2.14 and Section 2.3): psi [nz][ny][nx] in [0, 1]
  * and cos_theta [N-1][nz][ny][nx]: cos of the contact angle theta_iN of
  * phase i against phase N, measured inside phase i (eqs. 2.7-2.9), each in
- * [-1, 1]; NULL means 90 degrees everywhere. Must precede ddcc_init_fields. */
+ * [-1, 1]; NULL means 90 degrees everywhere. Must precede ddcc_init_fields.
+ * The calls that take or fill host arrays share (N + dim + 1) float64 planes
+ * of device memory, made by the first of them that needs it and kept with the
+ * context; boxes of up to 2^20 nodes use it for geometry too, larger ones, and
+ * walls that do not fit it, take memory for the call. Synchronises. */
 int ddcc_init_geometry(ddcc_ctx* ctx, const double* psi,
                        const double* cos_theta);
 
@@ -156,7 +163,15 @@ int ddcc_init_fields_dev(ddcc_ctx* ctx, const double* C_dev,
  * chemical potential mu_i, and one z-marching kernel for the node update.
  * Contexts whose step moves more than the 256 MB memory-side cache run the
  * same kernels with nontemporal stores, and in 2D with the loads of a tile
- * issued earlier (same results bit for bit). */
+ * issued earlier (same results bit for bit).
+ * Boxes of up to 2^17 nodes: once the context has taken 128 steps, a call for
+ * 24 or more launches most of them as captured groups of 64 and 16 steps (HIP
+ * graphs). The first calls that need a group make it, on a stream of the
+ * context's own and without waiting for the device; that takes some host time
+ * and memory of the runtime's. At most four groups per tile height are made;
+ * they are kept until ddcc_destroy. Calls for fewer than 24 steps, and calls on
+ * a stream that the caller is capturing, launch every step by itself, and so
+ * does every call where the runtime refuses a group. */
 int ddcc_step(ddcc_ctx* ctx, int64_t nsteps);
 
 /* C_i, u and P of the current time level (moment recovery of Section 3 and
@@ -269,10 +284,13 @@ int ddcc_adjoint(ddcc_ctx* ctx, int64_t nsteps, int interval, int phase,
 int ddcc_objective(ddcc_ctx* ctx, int phase, const double* weight, double* J);
 
 /* Kernel launch shape of the step kernel: tile (tx, ty) of nodes per
- * workgroup; 0 keeps the default. tx is 64 (one wavefront per row); ty is
- * 2, 4, 8 or 16 in 2D (default 4 for DDCC_FP64, 8 otherwise, and 2 or 4
- * for boxes that leave the chip partly idle) and 2 or 4 in 3D (default 4). Any other value returns DDCC_E_INVAL. Takes effect on
- * the next ddcc_step; results do not depend on the tile. */
+ * workgroup; 0 keeps the one that is set. tx is 64 (one wavefront per row).
+ * In 2D ty is 2, 4, 8 or 16 (default 4 for DDCC_FP64, 8 otherwise, and 2 or 4
+ * for boxes that leave the chip partly idle). In 3D ty is 2 or 4; 4, the
+ * default, stands for tiles of 256 nodes: 64 x 4, or 32 x 8 in steps of boxes
+ * at most 32 nodes wide and of DDCC_FP64 boxes up to 160 nodes wide where
+ * those leave fewer lanes idle. Any other value returns DDCC_E_INVAL. Takes
+ * effect on the next ddcc_step; results do not depend on the tile. */
 int ddcc_set_tile(ddcc_ctx* ctx, int tx, int ty);
 
 /* Times `steps` steps (after two untimed ones) with each tile height (2, 4,
