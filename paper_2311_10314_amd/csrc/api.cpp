@@ -838,6 +838,14 @@ int ddcc_create(const ddcc_params* p, void* stream, ddcc_ctx** out) {
   return rc;
 }
 
+static int ensure_geo64(ddcc_ctx* c) {
+  if (c->geo64) return DDCC_OK;
+  const size_t count = (size_t)c->p.nphase * c->n;
+  HIPCHK(c, hipMalloc(&c->geo64, count * sizeof(double)),
+         "hipMalloc float64 geometry");
+  return DDCC_OK;
+}
+
 // Geometry of K walls from float64 device arrays psik [K][n] and ctk
 // [K][N-1][n] (NULL: 90 degrees): psi and the wetting weights in the
 // context's field precision.
@@ -864,9 +872,8 @@ static int geometry_from_device(ddcc_ctx* c, int K, const double* psik,
   // adjoint supports) keep the float64 psi and cosines.
   if (c->p.dim == 2 && K == 1) {
     const size_t n = (size_t)c->n;
-    if (!c->geo64)
-      HIPCHK(c, hipMalloc(&c->geo64, (size_t)(nm1 + 1) * n * sizeof(double)),
-             "hipMalloc float64 geometry");
+    const int rc = ensure_geo64(c);
+    if (rc) return rc;
     e = hipMemcpyAsync(c->geo64, psik, n * sizeof(double),
                        hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess)
@@ -913,13 +920,17 @@ int ddcc_init_geometry_walls(ddcc_ctx* c, int nwalls, const double* psi,
   // of 0.1 after other streams' work, 256^2.)
   constexpr long long kKeepNodes = 1 << 20;
   const size_t room = (size_t)(c->p.nphase + c->p.dim + 1) * n;
-  const bool keep = c->nodes <= kKeepNodes && np + nc <= room;
+  bool keep = c->nodes <= kKeepNodes && np + nc <= room;
   double* d = nullptr;
   if (keep) {
+    // what the geometry needs anyway comes first
+    if (c->p.dim == 2 && nwalls == 1 && (rc = ensure_geo64(c))) return rc;
     rc = ensure_staging(c);
-    if (rc) return rc;
+    if (rc && rc != DDCC_E_NOMEM) return rc;
+    keep = rc == DDCC_OK;  // else there may be room for the walls alone
     d = c->staging;
-  } else {
+  }
+  if (!keep) {
     HIPCHK(c, hipMalloc(&d, (np + nc) * sizeof(double)), "hipMalloc geometry");
   }
   hipError_t e = hipMemcpyAsync(d, psi, np * sizeof(double),

@@ -368,3 +368,16 @@ def test_no_wide_kernel_is_built_that_nothing_launches(fake):
     assert len(wide) > 0
     assert not [w for w in wide if "double, double, double" in w
                 and w.endswith(", 4")]
+
+
+def test_geometry_needs_memory_for_its_walls_only(fake):
+    """The planes that host-array calls share do not fit, the walls do."""
+    shape = (64, 128)
+    p = fake.d.make_params(2, shape, 3, "D2Q9", "D2Q9", "fp64")
+    s = fake.d.Sim(p)
+    plane = 8 * 64 * 128
+    # psi and two angles; float64 psi and angles that stay for the adjoint
+    fake.set("memory", fake.get("allocated") + 6 * plane + 1000)
+    s.init_geometry(np.ones(shape), np.zeros((2,) + shape))
+    fake.set("memory", 0)
+    s.close()
