@@ -903,7 +903,8 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
   // 1.655 -> 1.772 ms, BF16 1.696 -> 1.807 ms). FP64 (253 VGPRs without it)
   // has no room.
   // The 16-bit storages take it with three phases, whose LDS ring leaves two
-  // waves per SIMD either way (130 x 75 x 101 D3Q7 FP16 323 -> 217 us).
+  // waves per SIMD either way (us per step: 130 x 75 x 101 D3Q7 FP16 316 -> 186,
+  // 110 x 100 x 90 D3Q15 FP16 319 -> 261, 128^3 D3Q15 BF16 575 -> 382).
   using In = NodeIn<N, LF, LG, Pop, S>;
   constexpr bool PF =
       (std::is_same_v<Pop, float> || (sizeof(Pop) == 2 && N == 3)) &&
@@ -994,15 +995,19 @@ void k_step3d(Coef<double> kda, Coef<R> ka,
 // in ceil(workgroups / slots) rounds, and a round lasts as long as its planes
 // plus the start of a column, `start` planes' worth: shorter columns fill an
 // idle chip or an emptier last round, longer ones start less often. Columns
-// of ZB, 4, 2 and 1 planes in k_step3d, us per step (same GPU): 64^3 FP64 141
-// / 92 / 83 / 85, FP32 77 / 54 / 45 / 51; 40^3 FP16 79 / 45 / 31 / 26; 130 x 75
-// x 101 N = 3 D3Q7 FP32 272 / 247 / 242 / 259; 110 x 100 x 90 N = 3 D3Q15 FP32
-// 373 / 325 / 306 / 310; 128^3 FP32 312 / 310 / 318 / 334 (there and above
-// every round is full and ZB stays). A shorter column has to promise 15 %:
-// other contexts' work may fill the idle units, and then the starts are what
-// is left (45 x 109 x 87 D3Q7 FP32, 8 -> 2 planes: alone 85 -> 75 us, three
-// contexts at once 61 -> 64). Boxes of odd width here and below: timed before
-// their rows were padded, both sides alike.
+// of ZB, 4, 2 and 1 planes in k_step3d, us per step (same GPU, one context, on
+// the present row pitch): 64^3 FP64 141 / 93 / 83 / 87, FP32 71 / 54 / 44 / 49;
+// 40^3 FP16 75 / 46 / 31 / 27; 130 x 75 x 101 N = 3 D3Q7 FP32 215 / 197 / 210 /
+// 218; 110 x 100 x 90 N = 3 D3Q15 FP32 306 / 269 / 254 / 265; 128^3 FP32 309 /
+// 310 / 320 / 332 (there and above every round is full and ZB stays). A
+// shorter column has to promise 15 %: other contexts' work may fill the idle
+// units, and then the starts are what is left (each of three contexts at once,
+// ZB -> the columns taken: 130 x 75 x 101 as above 166 -> 171, 192 x 90 x 28 N =
+// 3 FP64 182 -> 187 with 263 -> 205 alone; 45 x 109 x 87 D3Q7 FP32 with 2 planes,
+// not taken, alone 74 -> 69, at once 61 -> 63). In k_mu3d, a tenth of a step,
+// the same rule gives a context alone 1 to 15 % of the step and takes up to 5 %
+// of it from three at once (40^3 FP32 33/17.5 -> 28/17.0, 80 x 90 x 69 FP32
+// 131/91 -> 127/96, 128^3 312/297 -> 308/298).
 inline int planes_per_group(int nz, int tiles, int slots, double start,
                             int least) {
   int best = ZB;
