@@ -167,11 +167,12 @@ int ddcc_init_fields_dev(ddcc_ctx* ctx, const double* C_dev,
  * Boxes of up to 2^17 nodes: once the context has taken 128 steps, a call for
  * 24 or more launches most of them as captured groups of 64 and 16 steps (HIP
  * graphs). The first calls that need a group make it, on a stream of the
- * context's own and without waiting for the device; that takes some host time
- * and memory of the runtime's. At most four groups per tile height are made;
- * they are kept until ddcc_destroy. Calls for fewer than 24 steps, and calls on
- * a stream that the caller is capturing, launch every step by itself, and so
- * does every call where the runtime refuses a group. */
+ * context's own and without waiting for the device; that takes up to a few
+ * milliseconds of the host and 1.5 MB of device memory per context. At most
+ * four groups per tile height are made; they are kept until ddcc_destroy.
+ * Calls for fewer than 24 steps, and calls on a stream that the caller is
+ * capturing, launch every step by itself, and so does every call where the
+ * runtime refuses a group. */
 int ddcc_step(ddcc_ctx* ctx, int64_t nsteps);
 
 /* C_i, u and P of the current time level (moment recovery of Section 3 and
