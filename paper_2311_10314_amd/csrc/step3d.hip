@@ -1073,8 +1073,8 @@ hipError_t launch_3(const Coef<double>& kd, const Coef<R>& k,
 // 4 -> 32 x 8 tiles, one context / each of three at once):
 // - up to 72 and from 129 to 160 nodes (65 x 40 x 40 72/49 -> 61/43, 72 x 90 x
 //   64 244/156 -> 224/142, 129 x 60 x 90 264/241 -> 263/229, 132 x 160 x 100 N = 3
-//   1019/988 -> 981/906, 160 x 90 x 64 312/267 -> 291/261; the least gain of 36
-//   boxes alone is 0.4 % under zero, 160 x 160 x 100);
+//   1019/988 -> 981/906, 160 x 90 x 64 312/267 -> 291/261; the least gain of 96
+//   boxes alone is 0.5 % under zero, 140 x 60 x 90);
 // - 73 to 96 nodes, three tiles instead of two, where the 64 x 4 columns are more
 //   than two per compute unit (96 x 110 x 79 293/273 -> 279/234, 88 x 100 x 100
 //   325/283 -> 292/266, 80 x 160 x 100 473/442 -> 406/368), or where the shorter
